@@ -1635,8 +1635,11 @@ extern "C" int leyline_splice_contig(const leyline_cache* cache, int64_t seq_len
     int rc = plan_contig(cache, seq_len, dirs, n_dirs, &sched);
     if (rc) return rc;
     if (sched.ws_bytes > 0 && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) ||
-                               workspace_bytes < sched.ws_bytes))
-        return LEYLINE_E_WORKSPACE;
+                               workspace_bytes < sched.ws_bytes)) {
+        if (!sched.tiles_optional) return LEYLINE_E_WORKSPACE;
+        rc = plan_contig(cache, seq_len, dirs, n_dirs, &sched, false);
+        if (rc) return rc;
+    }
     return splice_contig_planned(cache, sched, dirs, new_len_out, device_status, static_cast<char*>(workspace),
                                  static_cast<hipStream_t>(stream));
 }
@@ -1689,7 +1692,11 @@ extern "C" int leyline_splice_contig_noalloc(const leyline_cache* cache, int64_t
     ContigSchedule sched;
     int rc = plan_contig(cache, seq_len, dirs, n_dirs, &sched);
     if (rc) return rc;
-    if (sched.ws_bytes > LEYLINE_SCRATCH_BYTES) return LEYLINE_E_WORKSPACE;
+    if (sched.ws_bytes > LEYLINE_SCRATCH_BYTES) {
+        if (!sched.tiles_optional) return LEYLINE_E_WORKSPACE;
+        rc = plan_contig(cache, seq_len, dirs, n_dirs, &sched, false);
+        if (rc) return rc;
+    }
     hipStream_t s = static_cast<hipStream_t>(stream);
     char* ws = nullptr;
     if (sched.ws_bytes > 0) {
@@ -1823,6 +1830,9 @@ extern "C" int leyline_splice_paged(const leyline_cache* cache, int32_t n_seqs, 
     if (int64_t(t.n_rows) + t.n_remap > INT32_MAX - 1024) return LEYLINE_E_INVAL;
     const bool row_table = t.n_rows > KINLINE_ROWS;       // else the gather resolves its rows
     for (int p = 0; p < n_planes; ++p) {
+        // 31-bit unit numbers: a half-split row has fewer two-chunk units than chunks
+        if (planes[p].neox_lanes && int64_t(t.n_rows) * planes[p].tpr > INT32_MAX - 1024)
+            use_two_chunk_units(planes[p]);
         if (int64_t(t.n_rows) * planes[p].tpr > INT32_MAX - 1024) return LEYLINE_E_INVAL;
         if (int64_t(t.n_remap) * cache->page_size * planes[p].rot_tpr > INT32_MAX - 1024) return LEYLINE_E_INVAL;
     }

@@ -8,6 +8,7 @@
 #include <cmath>
 #include <cstring>
 #include <map>
+#include <numeric>
 
 namespace leyline {
 
@@ -22,6 +23,12 @@ int elem_size(int32_t dtype) {
 }
 
 }  // namespace
+
+void use_two_chunk_units(KPlane& k) {
+    k.neox_lanes = k.neox_dpp = 0;
+    k.tpr = k.row_chunks - k.n_heads * (k.rot_chunks / 2);
+    k.tpr_div = make_div(k.tpr);
+}
 
 KDiv make_div(int32_t d) {
     int32_t l = 0;
@@ -86,19 +93,21 @@ int describe_cache(const leyline_cache* cache, bool paged, KPlane out[LEYLINE_MA
             cs_off += pl.rot_dim / 2;
             if (neox) {
                 // Lane exchange in the row kernels: a wavefront covers 64 consecutive chunks of
-                // the rows laid end to end, so every band must sit inside one 64-chunk window.
-                bool ok = false;
-                if (k.row_chunks % 64 == 0) {
-                    ok = true;
-                    for (int h = 0; h < k.n_heads; ++h) {
-                        const int32_t lo = h * k.head_chunks + k.rot_lo, hi = lo + k.rot_chunks - 1;
-                        if (lo / 64 != hi / 64) ok = false;
-                    }
-                } else if (64 % k.row_chunks == 0) {
-                    ok = true;
+                // the rows laid end to end.  Rows start at multiples of g = gcd(row_chunks, 64) of
+                // a wavefront's lanes, so a band inside one g-chunk window of its row never
+                // crosses a wavefront's end: whole rows of 64 chunks or of a divisor of it, and
+                // rows that are a multiple of their aligned bands (MLA rows of 72 chunks with an
+                // 8-chunk band at 64; 5 or 10 heads of 128).  8,192-token 27-layer half-split MLA
+                // cache, one message edit: two-chunk units in ordered chains 141 us, lane exchange
+                // in ordered tiles 87 us (5.4 TB/s).
+                const int32_t g = std::gcd(k.row_chunks, 64);
+                bool ok = true;
+                for (int h = 0; h < k.n_heads; ++h) {
+                    const int32_t lo = h * k.head_chunks + k.rot_lo, hi = lo + k.rot_chunks - 1;
+                    if (lo / g != hi / g) ok = false;
                 }
                 k.neox_lanes = ok ? 1 : 0;
-                if (!ok) k.tpr = k.row_chunks - k.n_heads * (k.rot_chunks / 2);
+                if (!ok) use_two_chunk_units(k);
                 // every kernel lays a lane's chunk at lane mod 16 of its 16-chunk group when rows
                 // (row kernels) or bands (rotary-only kernels) are multiples of 16 chunks
                 k.neox_dpp = (ok && k.rot_chunks == 16 && k.head_chunks % 16 == 0 && k.rot_lo % 16 == 0 &&
@@ -297,7 +306,7 @@ int plan_tiles(const leyline_cache* cache, const leyline_directive* dirs, const 
 }  // namespace
 
 int plan_contig(const leyline_cache* cache, int64_t seq_len, const leyline_directive* dirs,
-                int32_t n_dirs, ContigSchedule* out) {
+                int32_t n_dirs, ContigSchedule* out, bool allow_tiles) {
     KPlane planes[LEYLINE_MAX_PLANES];
     int n_planes = 0;
     int rc = describe_cache(cache, false, planes, &n_planes);
@@ -319,7 +328,7 @@ int plan_contig(const leyline_cache* cache, int64_t seq_len, const leyline_direc
     if (new_len > cache->capacity) return LEYLINE_E_CAPACITY;
     out->new_len = new_len;
     out->launches.clear();
-    out->tiles = false;
+    out->tiles = out->tiles_optional = false;
     out->tile_launches.clear();
     out->cs.clear();
     out->ws_flags = out->ws_cs = out->ws_bytes = 0;
@@ -389,10 +398,12 @@ int plan_contig(const leyline_cache* cache, int64_t seq_len, const leyline_direc
     const int n_levels = *std::max_element(level.begin(), level.end()) + 1;
     // Ordered tiles need every plane to move single chunks (half-split bands whose partners
     // cannot be exchanged between lanes use ordered chains).
-    bool tiles_ok = true;
+    bool tiles_ok = allow_tiles;
     int64_t row_bytes_all = 0;
     for (int p = 0; p < n_planes; ++p) {
         if (planes[p].rot == KROT_NEOX && !planes[p].neox_lanes) tiles_ok = false;
+        if (planes[p].rot == KROT_NEOX && planes[p].row_chunks % 64 && 64 % planes[p].row_chunks)
+            out->tiles_optional = true;
         row_bytes_all += planes[p].row_bytes;
     }
     // Within a job, a left shift by m makes row x the destination of row x + m.  Splitting the
@@ -421,7 +432,11 @@ int plan_contig(const leyline_cache* cache, int64_t seq_len, const leyline_direc
             out->tile_launches.clear();
             rc = plan_tiles(cache, dirs, planes, n_planes, jobs, level, KTILE_SMALL_CHUNKS, out);
         }
-        return rc;
+        if (rc == LEYLINE_OK || !out->tiles_optional) return rc;
+        out->tiles = false;                     // more tiles than a launch numbers: chains
+        out->tile_launches.clear();
+        out->cs.clear();
+        out->ws_flags = out->ws_cs = out->ws_bytes = 0;
     }
 
     const int32_t cs_need = cos_sin_per_shift(cache);

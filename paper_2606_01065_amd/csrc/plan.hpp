@@ -19,6 +19,9 @@ KDiv make_div(int32_t d);
 int describe_cache(const leyline_cache* cache, bool paged, KPlane out[LEYLINE_MAX_PLANES],
                    int* n_planes);
 
+// A half-split plane moved as two-chunk units (fewer units per row, no lane exchange).
+void use_two_chunk_units(KPlane& k);
+
 // Validation of one sequence's directives (already restricted to that sequence, FORGET already
 // resolved).
 int check_sequence(int64_t seq_len, const leyline_directive* dirs, int32_t n_dirs,
@@ -68,6 +71,9 @@ struct ContigSchedule {
     // Ordered tiles (used for every job of a call once any move needs them): launches in order,
     // after prep launches that clear the workspace and write the cos/sin table into it.
     bool tiles = false;
+    // Half-split rows that are neither whole wavefronts nor a divisor of one: the call also runs
+    // without tiles (rounds, or ordered chains that need no workspace), for callers that bring none.
+    bool tiles_optional = false;
     std::vector<TileLaunchHost> tile_launches;
     std::vector<KCosSin> cs;    // the call's cos/sin table (tiles)
     int64_t ws_flags = 0;       // workspace byte offsets: ticket counters (256 bytes per tile
@@ -78,8 +84,9 @@ struct ContigSchedule {
 // Tiles of one ordered-tile move on a plane with `tpr` chunks per row.
 int64_t tile_count(int64_t rows, int32_t tpr, int32_t tile_chunks);
 
+// allow_tiles = false: rounds and ordered chains only (no workspace).
 int plan_contig(const leyline_cache* cache, int64_t seq_len, const leyline_directive* dirs,
-                int32_t n_dirs, ContigSchedule* out);
+                int32_t n_dirs, ContigSchedule* out, bool allow_tiles = true);
 
 // ------------------------------------------------------------------------------------------
 // Paged splice.

@@ -1,0 +1,62 @@
+"""Which half-split rows have their partner chunks exchanged between lanes: on the host the
+planner's choice (tests/lane_exchange_check.cpp), on the GPU rows that are neither whole wavefronts
+nor a divisor of one, against the oracle, with and without room for the ordered tiles' flags."""
+
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+import torch
+
+import workloads as W
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_planner_exchanges_only_within_a_wavefront(tmp_path):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    exe, csrc = str(tmp_path / "check"), os.path.join(ROOT, "paper_2606_01065_amd", "csrc")
+    subprocess.run([gxx, "-O2", "-std=c++17", "-Wall", "-Wextra", "-Werror", "-I" + os.path.join(ROOT, "include"),
+                    "-I" + csrc, os.path.join(ROOT, "tests", "lane_exchange_check.cpp"),
+                    os.path.join(csrc, "plan.cpp"), "-o", exe], check=True)
+    out = subprocess.run([exe], capture_output=True, text=True)
+    assert out.returncode == 0, (out.returncode, out.stdout)
+    lanes = [tuple(map(int, ln.split())) for ln in out.stdout.split("\n") if ln]
+    assert lanes == [(1, 1), (1, 1), (1, 0), (1, 1), (1, 1), (1, 1), (1, 0), (1, 0),
+                     (0, 0), (0, 0), (0, 0), (0, 0), (0, 0)]
+
+
+KINDS = {"mla": [W.PlaneDesc((576,), 1, 576, 512, 64, 1, 10000.0)],
+         "heads5": W.gqa_planes(heads=5, dim=128), "heads10": W.gqa_planes(heads=10, dim=64),
+         "partial": [W.PlaneDesc((3, 64), 3, 64, 32, 32, 1, 10000.0)],
+         "heads96": W.gqa_planes(heads=3, dim=96)}                    # two-chunk units, ordered chains
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind,dtype", [("mla", "bf16"), ("mla", "f32"), ("heads5", "bf16"), ("heads10", "bf16"),
+                                        ("heads10", "f32"), ("partial", "bf16"), ("heads96", "bf16")])
+def test_ragged_half_split_rows(kind, dtype):
+    from paper_2606_01065_amd import leyline as L
+    from tests import test_gpu_contig as TC
+    rng = random.Random(f"{kind}/{dtype}")
+    for n, dirs in [(65, [W.Dir(3, 4, 0)]), (700, [W.Dir(30, 31, 0)]), (700, [W.Dir(100, 100, 3)]),
+                    (1500, [W.Dir(7, 40, 12), W.Dir(300, 310, 50), W.Dir(900, 1000, 1)]), (900, [W.Dir(10, 500, 16)])]:
+        wl = TC._small_workload(rng, "heads", dtype, 3, n, dirs)
+        wl.planes = KINDS[kind]
+        planes, stubs = W.alloc_contig(wl, "cuda:0")
+        pristine = [t.clone() for t in planes]
+        new_len = TC._run_and_check(L, wl, planes, stubs, f"ragged {kind}/{dtype} n={n}")
+        # a workspace too small for the tiles' flags: the same rows without tiles
+        cache = L.make_cache(TC._specs(L, wl, pristine))
+        dd = L.make_directives(TC._dir_dicts(wl, stubs))
+        small = torch.empty(256, dtype=torch.uint8, device="cuda:0")
+        assert L.leyline_splice_contig(cache, n, dd, len(dirs), workspace=small) == new_len
+        # one storage step, or 2e-6 of a pair's norm (below 10 here) where it nearly cancels: the two
+        # unit layouts may contract the pair's products in another order
+        for a, b in zip(planes, pristine):
+            torch.testing.assert_close(a[:, :new_len], b[:, :new_len], rtol=2.0 ** (-7 if dtype == "bf16" else -22),
+                                       atol=2e-5, msg=f"{kind}/{dtype} n={n}: with and without tiles")
