@@ -883,10 +883,10 @@ __global__ __launch_bounds__(PAGED_TPB) void rotate_rows_kernel(const KRotatePar
 // kernel (rows laid end to end, one 16-byte chunk per thread, so a wavefront reads one row entry
 // and moves whole lines); its last blocks rotate the rotary bands of REMAP pages (re-used whole
 // pages) in place, each looking its pages up in the plan and the old block table (or reading
-// them from paged_remap_order_kernel's physical-order list).  The rows of a small gather
-// (token-slot splices: the replacement rows) are resolved by the gathering blocks themselves, and
-// the new block tables and freed list are written by blocks between the two: one launch per call.
-// A large gather first runs paged_resolve_kernel, which expands the page runs once for all layers
+// them from paged_remap_order_kernel's physical-order list).  The rows of a gather of up to
+// KORDER_BYTES are resolved by the gathering blocks themselves, and the new block tables and freed
+// list are written by blocks between the two: one launch per call.  A larger gather first runs
+// paged_resolve_kernel, which expands the page runs once for all layers
 // and planes into a row table (for every row of every ASSEMBLE page: which old physical page and
 // row, or which replacement token, it comes from, which fresh page it goes to, which shift
 // re-anchors it) and writes the block tables and the freed list; paged_order_kernel before it
@@ -1177,6 +1177,100 @@ __device__ __forceinline__ KRowMove row_entry(const KPagedParams& P, const PlanV
     return e;
 }
 
+// A plan entry at a block-uniform address: read with scalar loads (the plan is constant while the
+// kernel runs).
+template <class T> __device__ __forceinline__ T plan_entry(const T* p) {
+    T v;
+    __builtin_memcpy(&v, (const __attribute__((address_space(4))) T*)p, sizeof(T));
+    return v;
+}
+
+// ASSEMBLE rows [i0, i1] of the call in plan order, seen as a whole (block-uniform): one run of one
+// sequence and one segment of its new rows (a replacement, or rows of one shift) when `one`.
+//
+// A gathering workgroup waits for its rows' pages before it can issue a data load, so what counts is
+// the number of dependent loads before that.  Its 256 chunks lie in a few consecutive rows, which
+// are nearly always rows of one run and one segment: the plan's part is then the same for all of
+// them and comes through the scalar cache, and each lane loads its free-list and block-table entry
+// at once, the one vector load that a row table would take too.  Resolving every lane by itself
+// (row_entry: a run search, a directive search, divisions, two more levels of vector loads) is kept
+// for workgroups across a boundary.  One-launch gathers, every lane by itself / by span: 131K MLA
+// sequence 4.32 / 2.32 ms (row table without order: 2.30), 105 MB of 32-token pages 39.6 / 27.5 us
+// (row table and order, three launches: 32.5).
+struct GatherSpan {
+    bool one;
+    int32_t seq, q_off, new_len;   // new position of row i: i + q_off
+    int32_t src_off;               // its old position, or its replacement row: i + src_off
+    int32_t cs;                    // first cos/sin entry (-1: not rotated)
+    int32_t dir;                   // replacement rows: directive index, else -1
+};
+
+__device__ __forceinline__ GatherSpan gather_span(const KPagedParams& P, const PlanView& V, int32_t i0, int32_t i1) {
+    const int32_t t0 = fdiv(i0, P.page_div), t1 = fdiv(i1, P.page_div);
+    int32_t lo = 0, hi = P.n_asm_runs;
+    while (hi - lo > 1) {
+        const int32_t mid = (lo + hi) >> 1;
+        if (plan_entry(&V.asm_runs[mid].ord0) <= t0) lo = mid; else hi = mid;
+    }
+    const KPageRun R = plan_entry(V.asm_runs + lo);
+    const KSeqEntry S = plan_entry(V.seqs + R.seq);
+    GatherSpan g;
+    g.seq = R.seq;
+    g.new_len = S.new_len;
+    g.q_off = (R.k0 - R.ord0) * P.page_size;
+    g.src_off = g.q_off;
+    g.cs = g.dir = -1;
+    const int64_t q0 = int64_t(i0) + g.q_off, q1 = int64_t(i1) + g.q_off;
+    // last directive whose replacement starts at or before q0, and where its segment ends
+    int32_t jlo = 0, jhi = S.dir_count;
+    while (jlo < jhi) {
+        const int32_t mid = (jlo + jhi) >> 1;
+        if (plan_entry(&V.dirs[S.dir_begin + mid].stub_start) <= q0) jlo = mid + 1; else jhi = mid;
+    }
+    int64_t end = jlo < S.dir_count ? plan_entry(&V.dirs[S.dir_begin + jlo].stub_start) : INT64_MAX;
+    if (jlo > 0) {
+        const int32_t j = S.dir_begin + jlo - 1;
+        const int64_t stub0 = plan_entry(&V.dirs[j].stub_start), stub1 = stub0 + plan_entry(&V.dirs[j].stub_len);
+        if (q0 < stub1) {
+            g.dir = j;
+            g.src_off = int32_t(g.q_off - stub0);
+            end = stub1;
+        } else {
+            g.src_off = int32_t(g.q_off - plan_entry(&V.dirs[j].delta));
+            g.cs = plan_entry(&V.dirs[j].cs);
+        }
+    }
+    g.one = t1 < R.ord0 + R.count && q1 < end;
+    return g;
+}
+
+// Row i of a span of one segment.
+__device__ __forceinline__ KRowMove gather_row(const KPagedParams& P, const GatherSpan& g, int32_t i) {
+    const int32_t task = fdiv(i, P.page_div);
+    KRowMove e{KROW_SKIP, 0, 0, i - task * P.page_size, -1, -1};
+    if (int64_t(i) + g.q_off >= g.new_len) return e;
+    const int32_t src = i + g.src_off;
+    int32_t pg = KROW_STUB, row = src;
+    const int32_t fp = task < P.n_free ? P.free_pages[task] : -1;
+    if (g.dir < 0) {
+        const int32_t k = fdiv(src, P.page_div);
+        row = src - k * P.page_size;
+        pg = P.bt_in[int64_t(g.seq) * P.bt_stride + k];
+        if (pg < 0 || pg >= P.capacity) pg = KROW_SKIP;
+    }
+    const bool bad = fp < 0 || fp >= P.capacity;
+    if (bad || pg == KROW_SKIP) {
+        if (P.status) atomicOr(P.status, int(LEYLINE_STATUS_BAD_PAGE));
+        return e;
+    }
+    e.src_page = pg;
+    e.src_row = row;
+    e.dst_page = fp;
+    e.cs = g.cs;
+    e.dir = g.dir;
+    return e;
+}
+
 // Entry w of the call's table work: the n_table new block-table entries, then the n_freed
 // freed-list entries.
 __device__ __forceinline__ void table_work(const KPagedParams& P, const PlanView& V, int64_t w) {
@@ -1205,14 +1299,29 @@ __device__ __forceinline__ void paged_move_block(const KPagedParams& P, const Pl
     int32_t i, u;
     row_unit(pl, true, t, P.n_rows, i, u);
     KRowMove e{KROW_SKIP, 0, 0, 0, -1, -1};
-    if (i < P.n_rows) e = INLINE ? row_entry(P, V, i) : P.rows[i];
-    const bool active = e.src_page != KROW_SKIP;
     // the cos/sin block of the workgroup's first row's shift, fetched before the data loads
     int32_t cs0 = -1;
-    if (pl.rot != KROT_NONE) {
-        const int32_t i0 = fdiv(tb, pl.tpr_div);
-        cs0 = INLINE ? row_entry(P, V, i0).cs : P.rows[i0].cs;
+    bool one = false;
+    if (INLINE) {
+        // the rows of this workgroup's units (packed layout: of its blocks of pack_groups rows)
+        const int32_t B = pl.pack_groups, last = min(tb + PAGED_TPB, P.n_rows * pl.tpr) - 1;
+        const int32_t i0 = B ? fdiv(tb, pl.pack_div) * B : fdiv(tb, pl.tpr_div);
+        const int32_t i1 = min(B ? fdiv(last, pl.pack_div) * B + B - 1 : fdiv(last, pl.tpr_div), P.n_rows - 1);
+        const GatherSpan g = gather_span(P, V, i0, i1);
+        one = g.one;
+        if (one) {
+            cs0 = g.cs;
+            if (i < P.n_rows) e = gather_row(P, g, i);
+        }
     }
+    if (!one) {
+        if (i < P.n_rows) e = INLINE ? row_entry(P, V, i) : P.rows[i];
+        if (pl.rot != KROT_NONE) {
+            const int32_t i0 = fdiv(tb, pl.tpr_div);
+            cs0 = INLINE ? row_entry(P, V, i0).cs : P.rows[i0].cs;
+        }
+    }
+    const bool active = e.src_page != KROW_SKIP;
     const CsReg c = cs_fetch(V.cs, cs0 + pl.cs_off, cs0 >= 0 ? pl.n_pairs : 0);
     // PAGED_LPT consecutive layers per thread: one row entry, all loads in flight before any store.
     const int layer0 = lgroup * PAGED_LPT;
@@ -1322,7 +1431,7 @@ __device__ __forceinline__ void paged_remap_block(const KPagedParams& P, const P
 }
 
 // One dimension of workgroups: the gather workgroups of every layer group first (plane by plane
-// within a layer group), then (small gathers) the workgroups that write the block tables and the
+// within a layer group), then (without a row table) the workgroups that write the block tables and the
 // freed list, then the REMAP workgroups of every layer group (plane by plane).  The gather's and
 // the tables' lookup chains are the longest, so they start first and the bulk of a token-slot
 // splice (the REMAP rotation) follows; planes without work get no workgroups.  SOLO: only plane 0
@@ -1828,7 +1937,6 @@ extern "C" int leyline_splice_paged(const leyline_cache* cache, int32_t n_seqs, 
     const KPagedTables& t = img.tables;
     char* ws = static_cast<char*>(workspace);
     if (int64_t(t.n_rows) + t.n_remap > INT32_MAX - 1024) return LEYLINE_E_INVAL;
-    const bool row_table = t.n_rows > KINLINE_ROWS;       // else the gather resolves its rows
     for (int p = 0; p < n_planes; ++p) {
         // 31-bit unit numbers: a half-split row has fewer two-chunk units than chunks
         if (planes[p].neox_lanes && int64_t(t.n_rows) * planes[p].tpr > INT32_MAX - 1024)
@@ -1836,6 +1944,10 @@ extern "C" int leyline_splice_paged(const leyline_cache* cache, int32_t n_seqs, 
         if (int64_t(t.n_rows) * planes[p].tpr > INT32_MAX - 1024) return LEYLINE_E_INVAL;
         if (int64_t(t.n_remap) * cache->page_size * planes[p].rot_tpr > INT32_MAX - 1024) return LEYLINE_E_INVAL;
     }
+    int64_t row_bytes = 0;
+    for (int p = 0; p < n_planes; ++p) row_bytes += planes[p].row_bytes;
+    const bool row_table = t.n_rows > KINLINE_ROWS && t.n_asm >= KORDER_MIN &&
+                           2 * row_bytes * t.n_rows * cache->n_layers >= KORDER_BYTES;
     if (t.upload > INT32_MAX) return LEYLINE_E_INVAL;
     const bool inline_plan = t.upload <= KPLAN_INLINE;
     if (!inline_plan) {
@@ -1865,6 +1977,7 @@ extern "C" int leyline_splice_paged(const leyline_cache* cache, int32_t n_seqs, 
             P.rot_div[p] = make_div(std::max(1, planes[p].rot_tpr));
         }
         P.capacity = cache->capacity;
+        P.page_div = make_div(cache->page_size);
         // a plan small enough travels in the kernel arguments; otherwise it was uploaded above
         P.plan = inline_plan ? nullptr : ws;
         if (inline_plan) std::memcpy(P.blob, img.bytes.data(), size_t(t.upload));
@@ -1900,21 +2013,23 @@ extern "C" int leyline_splice_paged(const leyline_cache* cache, int32_t n_seqs, 
         const bool bf16 = cache->dtype == LEYLINE_BF16;
         const unsigned layer_groups = unsigned((cache->n_layers + PAGED_LPT - 1) / PAGED_LPT);
         if (row_table) {
-            if (t.n_asm >= KORDER_MIN) {
-                int32_t shift = 0;
-                while (((cache->capacity - 1) >> shift) >= KORDER_BUCKETS) ++shift;
-                P.order_shift = shift;
-                P.order = reinterpret_cast<int32_t*>(ws + t.off_order);
-                rc = launch(paged_order_kernel, dim3(1), s, P, ORDER_TPB);
-                if (rc) return rc;
-            }
+            int32_t shift = 0;
+            while (((cache->capacity - 1) >> shift) >= KORDER_BUCKETS) ++shift;
+            P.order_shift = shift;
+            P.order = reinterpret_cast<int32_t*>(ws + t.off_order);
+            rc = launch(paged_order_kernel, dim3(1), s, P, ORDER_TPB);
+            if (rc) return rc;
             rc = launch(paged_resolve_kernel, dim3(unsigned((int64_t(t.n_rows) + n_tables + TPB - 1) / TPB)), s, P);
             if (rc) return rc;
         } else {
             // the first data launch writes the tables, spread over its layer groups
             P.table_blocks = int32_t((n_tables + PAGED_TPB - 1) / PAGED_TPB);
         }
-        if (t.remap_sorted) {
+        int64_t rot_bytes = 0;                             // read and written by the REMAP rotation
+        for (int p = 0; p < n_planes; ++p)
+            rot_bytes += 2 * int64_t(planes[p].n_heads) * planes[p].rot_chunks * 16 * t.n_remap *
+                         cache->page_size * cache->n_layers;
+        if (t.remap_sorted && rot_bytes >= KREMAP_SORT_MIN_BYTES) {
             // wide rotary bands: the REMAP pages in physical order
             int32_t shift = 0;
             while (((cache->capacity - 1) >> shift) >= KORDER_BUCKETS) ++shift;
@@ -1926,7 +2041,7 @@ extern "C" int leyline_splice_paged(const leyline_cache* cache, int32_t n_seqs, 
             if (rc) return rc;
         }
         // data kernel, one launch: gather workgroups, then the REMAP workgroups of every rotary
-        // plane, then (small gathers) the table work
+        // plane, then (without a row table) the table work
         int64_t mb = 0, rb = 0;
         P.move_base[0] = P.remap_base[0] = 0;
         for (int p = 0; p < n_planes; ++p) {

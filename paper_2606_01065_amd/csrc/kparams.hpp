@@ -400,6 +400,7 @@ struct KPagedParams {
     int32_t order_shift;     // destination-order bucket = physical page >> order_shift
     KDiv remap_div[LEYLINE_MAX_PLANES];  // by page_size * rot_tpr (band units per REMAP page)
     KDiv rot_div[LEYLINE_MAX_PLANES];    // by rot_tpr (band units per row)
+    KDiv page_div;                       // by page_size
     int64_t capacity;                    // physical pages
     // plan tables: at `plan` (the workspace copy), or, when plan is null, in `blob` below (a plan
     // small enough to travel in the kernel arguments); byte offsets within either
@@ -439,13 +440,18 @@ struct KPagedParams {
     alignas(16) unsigned char blob[KPLAN_INLINE];
 };
 
-// A call assembling at most this many rows gathers them without a row table: each gathering
-// workgroup resolves its rows from the plan, and the whole call is one data launch.
+// Gathers.  A call that assembles more than KINLINE_ROWS rows in at least KORDER_MIN pages and
+// moves at least KORDER_BYTES (read and written) runs in destination-page order (neighbouring
+// physical pages processed together), from a row table written by two launches before the data
+// launch; every other call is one launch whose workgroups resolve their rows from the plan in plan
+// order.  The order is worth 3-5% of a large gather's time and costs 8-14 us.  Row table in
+// destination order / one launch, 61-layer MLA cache: 64-token pages 111 MB 32.5 / 25 us,
+// 374 MB 79.5 / 75.4, 845 MB 163 / 162, 1.85 GB 330 / 338, 12.6 GB 2190 / 2318; 16-token pages 843 MB
+// 165 / 168; token slots 842 MB 156 / 153, 1.85 GB 335 / 346.  KORDER_BUCKETS: buckets of pages,
+// counted in LDS.
 constexpr int32_t KINLINE_ROWS = 1024;
-
-// The gather is ordered by destination page (neighbouring physical pages processed together)
-// when a call assembles at least this many pages; KORDER_BUCKETS buckets of pages, counted in LDS.
 constexpr int32_t KORDER_MIN = 64;
+constexpr int64_t KORDER_BYTES = int64_t(640) << 20;
 constexpr int32_t KORDER_BUCKETS = 4096;
 
 // The REMAP rotation runs in physical-page order (resolved and bucket-sorted by a first kernel)
@@ -453,6 +459,10 @@ constexpr int32_t KORDER_BUCKETS = 4096;
 // per row (whole GQA K heads: neighbouring rows then share DRAM pages; narrow MLA bands gain
 // nothing from it).
 constexpr int32_t KREMAP_SORT_BYTES = 1024;
+// ... and the call rotates at least this many bytes (read and written), so that the order saves
+// more than its 7-17 us launch takes.  GQA token slots, sorted / plan order: 102 MB 27 / 23 us,
+// 225 MB in two layers 65 / 48, 318 MB 64 / 59, 786 MB 136 / 143, 1.7 GB 286 / 322.
+constexpr int64_t KREMAP_SORT_MIN_BYTES = int64_t(512) << 20;
 
 
 // n / d for 0 <= n < 2^31 with a KDiv (the kernels' multiply-shift division), on either side.

@@ -1,0 +1,71 @@
+"""The two routes of a paged gather and of the in-place rotation of wide bands around their sizes:
+one launch in plan order, or (640 MiB gathered, 512 MiB rotated, read and written) the row table in
+destination order and the physical-order sort.  Every layer of a pool holds the same rows, so the
+layer count alone takes a small splice across the bound: layer 0 is compared with the oracle and all
+other layers with layer 0, bit for bit."""
+
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import splice_oracle as O
+from tests import test_gpu_paged as TP
+from tests.parity_util import assert_rows_match, host, oracle_plane
+
+pytestmark = pytest.mark.gpu
+
+MIB = 1 << 20
+
+
+def _workload(page, kind, layers):
+    # sequence 0: shift -7 (gathered unless pages hold one token), then a whole number of pages;
+    # sequence 1: growth and two more directives a few rows apart; sequence 2: untouched
+    dirs = [W.Dir(40, 60, 13, seq=0), W.Dir(600, 600 + 2 * 48 + 7, 14, seq=0),
+            W.Dir(0, 5, 300, seq=1), W.Dir(9, 10, 1, seq=1), W.Dir(500, 700, 3, seq=1)]
+    planes = {"mla": [W.mla_plane()], "mla_half": [W.PlaneDesc((576,), 1, 576, 512, 64, 1, 10000.0)],
+              "gqa8": W.gqa_planes(heads=8, dim=128)}[kind]
+    return W.Workload(f"routes_{kind}", layers, "bf16", planes, dirs, [1300, 1300, 70], page_size=page, seed=page)
+
+
+def _bytes(wl, flags):
+    P, rows, remaps = wl.page_size, 0, 0
+    for p in O.plan_paged(wl.seq_lens, TP._odirs(wl), P, remap=not flags):
+        rows += P * sum(k == O.ASSEMBLE for k in p.kinds)
+        remaps += P * sum(k == O.REMAP for k in p.kinds)
+    rb = sum(p.row_elems for p in wl.planes) * 2
+    bb = sum(p.n_heads * p.rot_dim for p in wl.planes) * 2
+    return 2 * wl.n_layers * rows * rb, 2 * wl.n_layers * remaps * bb
+
+
+@pytest.mark.parametrize("page,kind,flags,layers", [
+    (1, "mla", 1, 3), (1, "mla", 1, 320), (3, "mla", 0, 3), (3, "mla", 0, 320), (16, "mla_half", 0, 3),
+    (16, "mla_half", 0, 320), (16, "gqa8", 0, 3), (16, "gqa8", 0, 120), (1, "gqa8", 0, 3), (1, "gqa8", 0, 80)])
+def test_both_routes(page, kind, flags, layers):
+    from paper_2606_01065_amd import leyline as L
+    wl = _workload(page, kind, 1)
+    plans = O.plan_paged(wl.seq_lens, TP._odirs(wl), page, remap=not flags)
+    spare = sum(k == O.ASSEMBLE for p in plans for k in p.kinds) + 3
+    pools1, bt, free, stubs1 = W.alloc_paged(wl, "cuda:0", spare_pages=spare)
+    before, bt_h, free_h = [host(p) for p in pools1], host(bt), host(free)
+    stubs_h = [[host(s).reshape(1, s.shape[1], p.row_elems) for s, p in zip(per, wl.planes)] for per in stubs1]
+    wl.n_layers = layers
+    moved, rotated = _bytes(wl, flags)
+    sorts = page == 1 and kind == "gqa8"
+    assert (rotated if sorts else moved) >= (512 if sorts else 640) * MIB if layers > 3 else moved < 640 * MIB
+    print(f"[case] routes page={page} {kind} layers={layers} gather {moved >> 20} MiB rotate {rotated >> 20} MiB",
+          flush=True)
+    pools = [p.expand(layers, *p.shape[1:]).contiguous() for p in pools1]
+    stubs = [[s.expand(layers, *s.shape[1:]).contiguous() for s in per] for per in stubs1]
+    bt_out, freed, new_lens = TP._run_gpu(L, wl, pools, bt, free, stubs, flags=flags)
+    planes = [oracle_plane(p) for p in wl.planes]
+    flat = [b.reshape(b.shape[0], b.shape[1], b.shape[2], -1) for b in before]
+    want, want_bt, want_lens, want_freed = O.splice_paged(flat, planes, "bf16", bt_h, wl.seq_lens, TP._odirs(wl),
+                                                          stubs_h, list(free_h), page, remap=not flags)
+    assert new_lens == want_lens
+    assert np.array_equal(host(bt_out), want_bt)
+    assert list(host(freed)) == want_freed
+    for pi, plane in enumerate(planes):
+        got = host(pools[pi][:1]).reshape(want[pi].shape)
+        assert_rows_match(got, want[pi], plane, "bf16", what=f"routes page={page} {kind} plane {pi}")
+        assert torch.equal(pools[pi], pools[pi][:1].expand_as(pools[pi])), "layers differ"
