@@ -1655,6 +1655,7 @@ static int splice_contig_planned(const leyline_cache* cache, const ContigSchedul
     // whether a (job, plane) item rotates (it then gets a cos/sin block: KItem::cs >= 0), and its
     // threads; every count must fit a 31-bit index
     const int32_t cs_need = cos_sin_per_shift(cache);
+    ShiftTable shifts(cache);
     auto item_rotates = [&](const ContigJobHost& j, int p) {
         return j.kind != KJOB_STUB && cs_need > 0 && planes[p].rot != KROT_NONE;
     };
@@ -1705,7 +1706,7 @@ static int splice_contig_planned(const leyline_cache* cache, const ContigSchedul
                     rc = flush();
                     if (rc) return rc;
                 }
-                const int32_t cs0 = (j.kind != KJOB_STUB && cs_need > 0) ? append_cos_sin(cache, j.delta, cs) : -1;
+                const int32_t cs0 = (j.kind != KJOB_STUB && cs_need > 0) ? shifts.append(j.delta, cs) : -1;
                 for (int p = 0; p < n_planes; ++p) {
                     const int64_t th = item_threads(j, p);
                     if (th == 0) continue;
@@ -1860,7 +1861,7 @@ extern "C" int leyline_rotate_delta(const leyline_cache* cache, int64_t delta,
     P.h.n_rows = n_rows;
     P.h.status = device_status;
     std::vector<KCosSin> cs;
-    append_cos_sin(cache, delta, cs);
+    ShiftTable(cache).append(delta, cs);
     std::copy(cs.begin(), cs.end(), P.cs);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool bf16 = cache->dtype == LEYLINE_BF16;

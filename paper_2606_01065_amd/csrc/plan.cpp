@@ -146,20 +146,29 @@ int32_t cos_sin_per_shift(const leyline_cache* cache) {
     return n;
 }
 
-int32_t append_cos_sin(const leyline_cache* cache, int64_t shift, std::vector<KCosSin>& table) {
+int32_t ShiftTable::append(int64_t shift, std::vector<KCosSin>& table) {
     const int32_t first = int32_t(table.size());
-    const double d = double(shift);   // exact: |shift| < 2^53
-    for (int p = 0; p < cache->n_planes; ++p) {
-        const leyline_plane& pl = cache->planes[p];
-        const int half = pl.rot_dim / 2;
-        for (int i = 0; i < half; ++i) {
+    if (theta_.empty()) {
+        const int32_t n = cos_sin_per_shift(cache_);
+        theta_.reserve(size_t(n));
+        for (int p = 0; p < cache_->n_planes; ++p) {
+            const leyline_plane& pl = cache_->planes[p];
             // theta_i = base^(-2i/d_rot) (RoFormer), or the caller's table
-            const double theta = pl.inv_freq ? pl.inv_freq[i]
-                                             : std::pow(pl.rope_base, -2.0 * i / pl.rot_dim);
-            const double phi = d * theta;
-            table.push_back(KCosSin{kcs_t(std::cos(phi)), kcs_t(std::sin(phi))});
+            for (int i = 0; i < pl.rot_dim / 2; ++i)
+                theta_.push_back(pl.inv_freq ? pl.inv_freq[i] : std::pow(pl.rope_base, -2.0 * i / pl.rot_dim));
         }
     }
+    if (last_.empty() || shift != last_shift_) {
+        last_.clear();
+        last_.reserve(theta_.size());
+        const double d = double(shift);   // exact: |shift| < 2^53
+        for (const double theta : theta_) {
+            const double phi = d * theta;
+            last_.push_back(KCosSin{kcs_t(std::cos(phi)), kcs_t(std::sin(phi))});
+        }
+        last_shift_ = shift;
+    }
+    table.insert(table.end(), last_.begin(), last_.end());
     return first;
 }
 
@@ -221,6 +230,17 @@ namespace {
 
 int64_t align256(int64_t v) { return (v + 255) & ~int64_t(255); }
 
+// Rotating narrow interleaved bands: tiles of whole packed blocks, units packed.
+bool packs_tiles(const KPlane& pl, bool move, int32_t tile_base) {
+    return LEYLINE_TILE_PACK && move && pl.pack_groups && pl.pack_groups * pl.tpr <= tile_base;
+}
+
+int32_t tile_chunks(const KPlane& pl, bool move, int32_t tile_base) {
+    if (!packs_tiles(pl, move, tile_base)) return tile_base;
+    const int32_t blk = pl.pack_groups * pl.tpr;
+    return (tile_base / blk) * blk;
+}
+
 // Every job of the call as ordered-tile items, in dependency-level order, packed into launches of
 // at most KTILE_MAX_ITEMS items.  An item waits (inside its launch) for the earlier moves of its
 // plane whose source rows it overwrites; items of earlier launches are finished by stream order.
@@ -233,6 +253,7 @@ int plan_tiles(const leyline_cache* cache, const leyline_directive* dirs, const 
     for (size_t k = 0; k < order.size(); ++k) order[k] = k;
     std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return level[a] < level[b]; });
     const bool any_rot = cos_sin_per_shift(cache) > 0;
+    ShiftTable shifts(cache);
     std::map<int64_t, int32_t> shift_cs;                     // shift -> first entry of its block
     int64_t n_flags = 0;
     TileLaunchHost cur;
@@ -250,7 +271,7 @@ int plan_tiles(const leyline_cache* cache, const leyline_directive* dirs, const 
             if (found != shift_cs.end()) {
                 cs0 = found->second;
             } else {
-                cs0 = append_cos_sin(cache, x.delta, out->cs);
+                cs0 = shifts.append(x.delta, out->cs);
                 shift_cs.emplace(x.delta, cs0);
             }
         }
@@ -270,13 +291,8 @@ int plan_tiles(const leyline_cache* cache, const leyline_directive* dirs, const 
                 it.stub = static_cast<const char*>(dirs[x.dir].stub[p]);
                 it.cs = -1;
             }
-            // rotating narrow interleaved bands: tiles of whole packed blocks, units packed
-            it.tile_chunks = tile_base;
-            const int32_t blk = planes[p].pack_groups * planes[p].tpr;
-            if (LEYLINE_TILE_PACK && move && it.cs >= 0 && planes[p].pack_groups && blk <= tile_base) {
-                it.tile_chunks = (tile_base / blk) * blk;
-                it.pack = 1;
-            }
+            it.tile_chunks = tile_chunks(planes[p], move, tile_base);
+            it.pack = packs_tiles(planes[p], move, tile_base) ? 1 : 0;
             const int64_t tiles = tile_count(x.count, planes[p].tpr, it.tile_chunks);
             const int64_t tickets = int64_t(cache->n_layers) * tiles;
             it.n_tiles = int32_t(tiles);
@@ -422,16 +438,14 @@ int plan_contig(const leyline_cache* cache, int64_t seq_len, const leyline_direc
     }
     if (tiles_ok && need_tiles) {
         // A call of few full-size tiles cannot fill the device and is bound by each tile's chain
-        // of latencies (ticket, loads, flag, stores): it is planned again with quarter-size tiles.
-        const size_t cs_before = out->cs.size();
-        int rc = plan_tiles(cache, dirs, planes, n_planes, jobs, level, KTILE_CHUNKS, out);
+        // of latencies (ticket, loads, flag, stores): it is planned with quarter-size tiles.
         int64_t tickets = 0;
-        for (const TileLaunchHost& tl : out->tile_launches) tickets += tl.tickets;
-        if (rc == LEYLINE_OK && tickets < KTILE_SMALL_TICKETS) {
-            out->cs.resize(cs_before);
-            out->tile_launches.clear();
-            rc = plan_tiles(cache, dirs, planes, n_planes, jobs, level, KTILE_SMALL_CHUNKS, out);
-        }
+        for (const ContigJobHost& x : jobs)
+            for (int p = 0; p < n_planes; ++p)
+                tickets += cache->n_layers * tile_count(x.count, planes[p].tpr,
+                                                        tile_chunks(planes[p], x.kind != KJOB_STUB, KTILE_CHUNKS));
+        rc = plan_tiles(cache, dirs, planes, n_planes, jobs, level,
+                        tickets < KTILE_SMALL_TICKETS ? KTILE_SMALL_CHUNKS : KTILE_CHUNKS, out);
         if (rc == LEYLINE_OK || !out->tiles_optional) return rc;
         out->tiles = false;                     // more tiles than a launch numbers: chains
         out->tile_launches.clear();
@@ -637,6 +651,7 @@ int build_paged_image(const leyline_cache* cache, const PagedPlan& plan, int32_t
     std::vector<KDirEntry> dtab(static_cast<size_t>(n_dirs));
     std::vector<KCosSin> cs;
     const bool any_rot = cos_sin_per_shift(cache) > 0;
+    ShiftTable shifts(cache);
     int32_t j0 = 0;
     for (int32_t b = 0; b < n_seqs; ++b) {
         int32_t j1 = j0;
@@ -657,7 +672,7 @@ int build_paged_image(const leyline_cache* cache, const PagedPlan& plan, int32_t
             de.stub_len = d.stub_len;
             shift += d.stub_len - (d.span_end - d.span_start);
             de.delta = shift;
-            de.cs = (shift != 0 && any_rot) ? append_cos_sin(cache, shift, cs) : -1;
+            de.cs = (shift != 0 && any_rot) ? shifts.append(shift, cs) : -1;
             for (int p = 0; p < cache->n_planes; ++p)
                 de.stub[p] = static_cast<const char*>(d.stub[p]);
         }

@@ -37,8 +37,20 @@ int resolve_forget(const leyline_directive* dirs, int32_t n_dirs, int32_t n_seqs
                    const leyline_directive** use);
 
 // cos/sin of (shift * theta_i), evaluated in fp64 and rounded to fp32, for every rotary pair of
-// every rotary plane, appended to `table`.  Returns the offset of the first entry.
-int32_t append_cos_sin(const leyline_cache* cache, int64_t shift, std::vector<KCosSin>& table);
+// every rotary plane.  The frequencies, a third of the cost, are evaluated once per call, and a shift
+// that repeats the one before it is copied.
+class ShiftTable {
+public:
+    explicit ShiftTable(const leyline_cache* cache) : cache_(cache) {}
+    // Appends the shift's block to `table`; returns the offset of its first entry.
+    int32_t append(int64_t shift, std::vector<KCosSin>& table);
+
+private:
+    const leyline_cache* cache_;
+    std::vector<double> theta_;
+    std::vector<KCosSin> last_;
+    int64_t last_shift_ = 0;
+};
 
 // Number of cos/sin entries one shift needs (sum over rotary planes of rot_dim / 2).
 int32_t cos_sin_per_shift(const leyline_cache* cache);

@@ -262,6 +262,11 @@ def make_directives(dirs: Sequence[dict]) -> ctypes.Array:
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
+        # the current stream's handle without the Stream object around it: 0.3 us a call instead of
+        # 2.7, beside 4.6 us for a whole one-launch call into the library
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None and torch.cuda.is_initialized():
+            return raw(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
