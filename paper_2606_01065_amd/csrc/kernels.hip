@@ -65,11 +65,10 @@ constexpr int TPB = LEYLINE_TPB;
 #define LEYLINE_MOVE_TPB 256
 #endif
 constexpr int CRPT = LEYLINE_CONTIG_RPT;   // rows per thread of a rotating round item
-// Rows per thread of a round-kernel item: CRPT when it rotates; with fp32 pairs one when it only
-// copies (a V plane, a replacement copy), with fp64 pairs CRPT as well (there the rotating
-// workgroups are bound by their pair arithmetic, and the GQA splice runs 4 points slower with
-// one-row copies beside them).  The kernel and the launcher's grid both take it from here.
-LEYLINE_HD inline int round_rows_per_thread(bool rotates) { return rotates || LEYLINE_PAIR_F64 ? CRPT : 1; }
+// Rows per thread of a round-kernel item: CRPT when it rotates, one when it only copies (a V plane, a
+// replacement copy); with fp64 pairs, copies of CRPT / one row: GQA 16K splice 575 / 556 us, split MLA
+// 32K splice 613 / 576 us.  The kernel and the launcher's grid both take it from here.
+LEYLINE_HD inline int round_rows_per_thread(bool rotates) { return rotates ? CRPT : 1; }
 constexpr int MOVE_TPB = LEYLINE_MOVE_TPB; // its workgroup size
 #ifndef LEYLINE_PAGED_TPB
 #define LEYLINE_PAGED_TPB 256
@@ -153,11 +152,57 @@ __device__ __forceinline__ float rot_own(float mine, float partner, const KCosSi
 #endif
 }
 
+#if LEYLINE_PAIR_F64
+// fp64 results to bf16 with one rounding, the cheap way: through the nearest-even float.  Rounding that
+// float to nearest-even bf16 gives the bf16 nearest to the fp64 value unless the float sits exactly
+// between two bf16 values (low half 0x8000, one result in 65,536), where the side the first rounding
+// came from decides; a chunk with such a float is done again through f32_round_odd, whose second
+// conversion, comparisons and selects every result paid for before.  These kernels are bound by that
+// arithmetic where every lane rotates: GQA token slots (786 MB) 185 -> 152 us, GQA rows in place (805 MB)
+// 156 -> 137 us, half-split tiles (474 MB) 128 -> 112 us, GQA tiles (497 MB) 110 -> 102 us.  The words of
+// a chunk are kept one after the other (sched_barrier): side by side they take 20 registers more, and
+// the gathers lose a wavefront in six.
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+
+// Packs two results; `mid` keeps the smallest low half ^ 0x8000 so far (0: some float was in between).
+__device__ __forceinline__ uint32_t pack_bf16_f64(double a, double b, u16x2& mid) {
+    const float x = float(a), y = float(b);
+    const uint32_t low = __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x05040100u) ^ 0x80008000u;
+    mid = __builtin_elementwise_min(mid, __builtin_bit_cast(u16x2, low));
+    return pack_bf16(x, y);
+}
+__device__ __forceinline__ bool any_between(u16x2 mid) { return mid.x == 0 || mid.y == 0; }
+// The chunk and its first entry as new values: the second time round the compiler would otherwise keep
+// every entry and converted input of the first in registers, for one chunk in 8,192.
+__device__ __forceinline__ void again(u32x4& v, int32_t& cs) {
+    asm volatile("" : "+v"(v), "+v"(cs));
+}
+#endif
+
 template <int ESZ> struct Elt { static constexpr int EPC = 16 / ESZ; };   // elements per chunk
 
 // Interleaved chunk: EPC/2 pairs (2i, 2i+1), cos/sin from table[cs + i].
 template <int ESZ> __device__ __forceinline__ void rot_interleaved(u32x4& v, const KCosSin* t, int32_t cs);
 template <> __device__ __forceinline__ void rot_interleaved<2>(u32x4& v, const KCosSin* t, int32_t cs) {
+#if LEYLINE_PAIR_F64
+    {
+#pragma clang fp contract(off)
+        u16x2 mid{0xffff, 0xffff};
+        u32x4 r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const KCosSin k = t[cs + i];
+            const double x = bf_lo(v[i]), y = bf_hi(v[i]);
+            r[i] = pack_bf16_f64(x * k.c - y * k.s, x * k.s + y * k.c, mid);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (!any_between(mid)) {
+            v = r;
+            return;
+        }
+        again(v, cs);
+    }
+#endif
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const KCosSin k = t[cs + i];
@@ -181,6 +226,28 @@ template <> __device__ __forceinline__ void rot_interleaved<4>(u32x4& v, const K
 // chunk `y`; EPC pairs with cos/sin table[cs + e].  Both chunks are updated.
 template <int ESZ> __device__ __forceinline__ void rot_halves(u32x4& x, u32x4& y, const KCosSin* t, int32_t cs);
 template <> __device__ __forceinline__ void rot_halves<2>(u32x4& x, u32x4& y, const KCosSin* t, int32_t cs) {
+#if LEYLINE_PAIR_F64
+    {
+#pragma clang fp contract(off)
+        u16x2 mid{0xffff, 0xffff};
+        u32x4 r, q;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const KCosSin k0 = t[cs + 2 * i], k1 = t[cs + 2 * i + 1];
+            const double a0 = bf_lo(x[i]), a1 = bf_hi(x[i]), b0 = bf_lo(y[i]), b1 = bf_hi(y[i]);
+            r[i] = pack_bf16_f64(a0 * k0.c - b0 * k0.s, a1 * k1.c - b1 * k1.s, mid);
+            q[i] = pack_bf16_f64(a0 * k0.s + b0 * k0.c, a1 * k1.s + b1 * k1.c, mid);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (!any_between(mid)) {
+            x = r;
+            y = q;
+            return;
+        }
+        again(x, cs);
+        again(y, cs);
+    }
+#endif
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const KCosSin k0 = t[cs + 2 * i], k1 = t[cs + 2 * i + 1];
@@ -225,6 +292,25 @@ template <int ESZ> __device__ __forceinline__ void rot_halves_own(u32x4& v, cons
                                                                   int32_t cs, bool lo);
 template <> __device__ __forceinline__ void rot_halves_own<2>(u32x4& v, const u32x4& o, const KCosSin* t,
                                                               int32_t cs, bool lo) {
+#if LEYLINE_PAIR_F64
+    {
+#pragma clang fp contract(off)
+        u16x2 mid{0xffff, 0xffff};
+        u32x4 r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const KCosSin k0 = t[cs + 2 * i], k1 = t[cs + 2 * i + 1];
+            r[i] = pack_bf16_f64(double(bf_lo(v[i])) * k0.c + double(bf_lo(o[i])) * (lo ? -k0.s : k0.s),
+                                 double(bf_hi(v[i])) * k1.c + double(bf_hi(o[i])) * (lo ? -k1.s : k1.s), mid);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (!any_between(mid)) {
+            v = r;
+            return;
+        }
+        again(v, cs);
+    }
+#endif
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const float m0 = rot_own<true>(bf_lo(v[i]), bf_lo(o[i]), t[cs + 2 * i], lo);
@@ -1438,6 +1524,9 @@ __device__ __forceinline__ void paged_remap_block(const KPagedParams& P, const P
 // has work in this launch, so no workgroup looks its plane up.  INLINE: the gather resolves its
 // rows (no row table) and the launch may carry table work.
 template <int ESZ, bool SOLO, bool INLINE>
+#if LEYLINE_PAIR_F64
+__attribute__((amdgpu_waves_per_eu(6)))   // 80 registers; 93 without the limit, one wavefront in six fewer
+#endif
 __global__ __launch_bounds__(PAGED_TPB) void paged_data_kernel(const KPagedParams P) {
     __shared__ KCosSin lcs[KMAX_CS];
     const PlanView V = plan_view(P);
