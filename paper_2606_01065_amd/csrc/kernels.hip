@@ -1280,7 +1280,9 @@ template <class T> __device__ __forceinline__ T plan_entry(const T* p) {
 // them and comes through the scalar cache, and each lane loads its free-list and block-table entry
 // at once, the one vector load that a row table would take too.  Resolving every lane by itself
 // (row_entry: a run search, a directive search, divisions, two more levels of vector loads) is kept
-// for workgroups across a boundary.  One-launch gathers, every lane by itself / by span: 131K MLA
+// for workgroups across a boundary, whose cos/sin block still comes from the span (found by a second
+// row_entry it made them slower than without spans: 256 three-row replacements in 27-layer MLA token
+// slots 68.7 us, no spans 64.8, now 61.7).  One-launch gathers, every lane by itself / by span: 131K MLA
 // sequence 4.32 / 2.32 ms (row table without order: 2.30), 105 MB of 32-token pages 39.6 / 27.5 us
 // (row table and order, three launches: 32.5).
 struct GatherSpan {
@@ -1387,25 +1389,22 @@ __device__ __forceinline__ void paged_move_block(const KPagedParams& P, const Pl
     KRowMove e{KROW_SKIP, 0, 0, 0, -1, -1};
     // the cos/sin block of the workgroup's first row's shift, fetched before the data loads
     int32_t cs0 = -1;
-    bool one = false;
     if (INLINE) {
-        // the rows of this workgroup's units (packed layout: of its blocks of pack_groups rows)
-        const int32_t B = pl.pack_groups, last = min(tb + PAGED_TPB, P.n_rows * pl.tpr) - 1;
-        const int32_t i0 = B ? fdiv(tb, pl.pack_div) * B : fdiv(tb, pl.tpr_div);
-        const int32_t i1 = min(B ? fdiv(last, pl.pack_div) * B + B - 1 : fdiv(last, pl.tpr_div), P.n_rows - 1);
-        const GatherSpan g = gather_span(P, V, i0, i1);
-        one = g.one;
-        if (one) {
-            cs0 = g.cs;
-            if (i < P.n_rows) e = gather_row(P, g, i);
+        bool one = false;
+        GatherSpan g{};
+        if (pl.rot != KROT_NONE || !P.short_spans) {
+            // the rows of this workgroup's units (packed layout: of its blocks of pack_groups rows)
+            const int32_t B = pl.pack_groups, last = min(tb + PAGED_TPB, P.n_rows * pl.tpr) - 1;
+            const int32_t i0 = B ? fdiv(tb, pl.pack_div) * B : fdiv(tb, pl.tpr_div);
+            const int32_t i1 = min(B ? fdiv(last, pl.pack_div) * B + B - 1 : fdiv(last, pl.tpr_div), P.n_rows - 1);
+            g = gather_span(P, V, i0, i1);
+            one = g.one;
+            cs0 = g.cs;                            // a row of another shift reads the plan's table
         }
-    }
-    if (!one) {
-        if (i < P.n_rows) e = INLINE ? row_entry(P, V, i) : P.rows[i];
-        if (pl.rot != KROT_NONE) {
-            const int32_t i0 = fdiv(tb, pl.tpr_div);
-            cs0 = INLINE ? row_entry(P, V, i0).cs : P.rows[i0].cs;
-        }
+        if (i < P.n_rows) e = one ? gather_row(P, g, i) : row_entry(P, V, i);
+    } else {
+        if (i < P.n_rows) e = P.rows[i];
+        if (pl.rot != KROT_NONE) cs0 = P.rows[fdiv(tb, pl.tpr_div)].cs;
     }
     const bool active = e.src_page != KROW_SKIP;
     const CsReg c = cs_fetch(V.cs, cs0 + pl.cs_off, cs0 >= 0 ? pl.n_pairs : 0);
@@ -2147,6 +2146,7 @@ extern "C" int leyline_splice_paged(const leyline_cache* cache, int32_t n_seqs, 
         if (blocks > INT32_MAX - 1024) return LEYLINE_E_INVAL;
         if (blocks > 0) {
             P.layer_groups = int32_t(layer_groups);
+            P.short_spans = short_gather_spans(t.n_rows, t.n_spans) ? 1 : 0;
             P.gather_split = cache->page_size >= LEYLINE_GATHER_SPLIT_PAGE ? 1 : 0;
             P.move_blk_div = make_div(int32_t(std::max<int64_t>(1, mb)));
             P.remap_blk_div = make_div(int32_t(std::max<int64_t>(1, rb)));

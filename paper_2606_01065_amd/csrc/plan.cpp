@@ -542,7 +542,7 @@ int plan_paged(int32_t page_size, int32_t n_seqs, const int32_t* seq_lens,
     out->run_begin.assign(size_t(n_seqs) + 1, 0);
     out->runs.clear();
     out->freed.clear();
-    int64_t n_fresh = 0, n_remap = 0, n_freed = 0;
+    int64_t n_fresh = 0, n_remap = 0, n_freed = 0, n_spans = 0;
 
     int32_t j0 = 0;
     std::vector<Piece> pieces;
@@ -595,8 +595,11 @@ int plan_paged(int32_t page_size, int32_t n_seqs, const int32_t* seq_lens,
         // A new page is re-used (IDENTITY for shift 0, REMAP for another multiple of the page
         // size) when all its valid rows lie in one old-row piece whose shift keeps in-page
         // offsets; every other page is ASSEMBLE.
+        size_t at = 0;                                   // first piece not before the run
         auto assemble = [&](int64_t k0, int64_t k1) {
             if (k1 <= k0) return;
+            while (at < pieces.size() && pieces[at].hi <= k0 * P) ++at;
+            for (size_t i = at; i < pieces.size() && pieces[i].lo < k1 * P; ++i) ++n_spans;
             out->runs.push_back(KPageRun{b, int32_t(k0), int32_t(k1 - k0), LEYLINE_PAGE_ASSEMBLE,
                                          int32_t(n_fresh), int32_t(n_fresh), -1, 0});
             n_fresh += k1 - k0;
@@ -641,6 +644,7 @@ int plan_paged(int32_t page_size, int32_t n_seqs, const int32_t* seq_lens,
     out->n_fresh = int32_t(n_fresh);
     out->n_remap = int32_t(n_remap);
     out->n_freed = int32_t(n_freed);
+    out->n_spans = int32_t(n_spans);             // at most one a row of the fresh pages
     return LEYLINE_OK;
 }
 
@@ -726,6 +730,7 @@ int build_paged_image(const leyline_cache* cache, const PagedPlan& plan, int32_t
     t.n_asm = plan.n_fresh; t.n_remap = plan.n_remap; t.n_freed = plan.n_freed;
     t.bt_stride = bt_stride;
     t.n_rows = int32_t(n_rows);
+    t.n_spans = plan.n_spans;
     t.remap_sorted = remap_sorted ? 1 : 0;
     img->bytes.assign(size_t(t.upload), 0);
     auto put = [&](int64_t at, const void* src, size_t bytes) {

@@ -116,6 +116,8 @@ struct PagedPlan {
     int32_t n_fresh = 0;               // ASSEMBLE pages (fresh pages consumed)
     int32_t n_remap = 0;
     int32_t n_freed = 0;
+    int32_t n_spans = 0;               // spans of ASSEMBLE rows: one page run and one segment (a
+                                       // replacement, or old rows of one shift)
 };
 
 // remap = false: copy-on-write (no page whose rows shift is re-used; such pages are assembled).

@@ -4,6 +4,8 @@ destination order and the physical-order sort.  Every layer of a pool holds the 
 layer count alone takes a small splice across the bound: layer 0 is compared with the oracle and all
 other layers with layer 0, bit for bit."""
 
+import random
+
 import numpy as np
 import pytest
 import torch
@@ -69,3 +71,42 @@ def test_both_routes(page, kind, flags, layers):
         got = host(pools[pi][:1]).reshape(want[pi].shape)
         assert_rows_match(got, want[pi], plane, "bf16", what=f"routes page={page} {kind} plane {pi}")
         assert torch.equal(pools[pi], pools[pi][:1].expand_as(pools[pi])), "layers differ"
+
+
+SHORT_KINDS = {"mla": [W.mla_plane()], "mla_split": W.mla_split_planes(), "gqa8": W.gqa_planes(heads=8, dim=128),
+               "mla_half": [W.PlaneDesc((576,), 1, 576, 512, 64, 1, 10000.0)], "heads96": W.gqa_planes(heads=3, dim=96)}
+
+
+@pytest.mark.parametrize("kind,dtype", [("mla", "bf16"), ("mla_split", "bf16"), ("gqa8", "bf16"), ("mla_half", "bf16"),
+                                        ("heads96", "bf16"), ("mla", "f32"), ("mla_split", "f32")])
+def test_many_short_spans(kind, dtype):
+    """Gathers whose spans (replacements and rows of one shift) hold one to a few rows, so that nearly every
+    workgroup lies across several, in one launch: whole pools against the oracle."""
+    from paper_2606_01065_amd import leyline as L
+    rng = random.Random(f"{kind}/{dtype}")
+    for page, flags in ((1, 0), (1, 1), (3, 0), (16, 0)):
+        dirs = []
+        for b in range(2):
+            at = rng.randint(0, 9)
+            for _ in range(60):
+                e = at + rng.randint(0, 3)
+                dirs.append(W.Dir(at, e, rng.randint(0, 3), seq=b))
+                at = e + rng.choice([1, 1, 2, 5, 12])
+        lens = [max(d.span_end for d in dirs if d.seq == b) + 7 for b in range(2)]
+        wl = W.Workload(f"short_{kind}", 3, dtype, SHORT_KINDS[kind], dirs, lens, page_size=page, seed=page)
+        plans = O.plan_paged(lens, TP._odirs(wl), page, remap=not flags)
+        print(f"[case] short spans {kind}/{dtype} page={page} flags={flags} lens={lens}", flush=True)
+        pools, bt, free, stubs = W.alloc_paged(wl, "cuda:0", spare_pages=3 + sum(k == O.ASSEMBLE for p in plans for k in p.kinds))
+        before, bt_h, free_h = [host(p) for p in pools], host(bt), host(free)
+        stubs_h = [[host(s).reshape(3, s.shape[1], p.row_elems) for s, p in zip(per, wl.planes)] for per in stubs]
+        bt_out, freed, new_lens = TP._run_gpu(L, wl, pools, bt, free, stubs, flags=flags)
+        planes = [oracle_plane(p) for p in wl.planes]
+        flat = [b.reshape(b.shape[0], b.shape[1], b.shape[2], -1) for b in before]
+        want, want_bt, want_lens, want_freed = O.splice_paged(flat, planes, dtype, bt_h, lens, TP._odirs(wl), stubs_h,
+                                                              list(free_h), page, remap=not flags)
+        assert new_lens == want_lens
+        assert np.array_equal(host(bt_out), want_bt)
+        assert list(host(freed)) == want_freed
+        for pi, plane in enumerate(planes):
+            assert_rows_match(host(pools[pi]).reshape(want[pi].shape), want[pi], plane, dtype,
+                              what=f"short spans {kind} page={page} plane {pi}")
