@@ -139,8 +139,11 @@ __device__ __forceinline__ void rot_pair(float& a, float& b, const KCosSin& k) {
 #endif
 }
 
-// One member of a half-split pair, on the lane that holds it: the low member a becomes
-// a c - b s, the high member b becomes b c + a s, i.e. mine * c + partner * (lo ? -s : s).
+// One member of a half-split pair: the low member a becomes a c - b s, the high member b becomes
+// b c + a s, i.e. mine * c + partner * (lo ? -s : s).  With fp32 pairs the partner's product is the
+// rounded one and the member's own is fused with the sum, written out because every route rotates
+// half-split bands with this function: whether a lane holds one member or both (two-chunk units)
+// then depends on the layout and the workspace, the stored bits do not.
 template <bool BF16>
 __device__ __forceinline__ float rot_own(float mine, float partner, const KCosSin& k, bool lo) {
 #if LEYLINE_PAIR_F64
@@ -148,7 +151,7 @@ __device__ __forceinline__ float rot_own(float mine, float partner, const KCosSi
     const double r = double(mine) * k.c + double(partner) * (lo ? -k.s : k.s);
     return BF16 ? f32_round_odd(r) : float(r);
 #else
-    return mine * k.c + partner * (lo ? -k.s : k.s);
+    return __builtin_fmaf(mine, k.c, partner * (lo ? -k.s : k.s));
 #endif
 }
 
@@ -251,22 +254,19 @@ template <> __device__ __forceinline__ void rot_halves<2>(u32x4& x, u32x4& y, co
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const KCosSin k0 = t[cs + 2 * i], k1 = t[cs + 2 * i + 1];
-        float a0 = bf_lo(x[i]), a1 = bf_hi(x[i]);
-        float b0 = bf_lo(y[i]), b1 = bf_hi(y[i]);
-        rot_pair<true>(a0, b0, k0);
-        rot_pair<true>(a1, b1, k1);
-        x[i] = pack_bf16(a0, a1);
-        y[i] = pack_bf16(b0, b1);
+        const float a0 = bf_lo(x[i]), a1 = bf_hi(x[i]);
+        const float b0 = bf_lo(y[i]), b1 = bf_hi(y[i]);
+        x[i] = pack_bf16(rot_own<true>(a0, b0, k0, true), rot_own<true>(a1, b1, k1, true));
+        y[i] = pack_bf16(rot_own<true>(b0, a0, k0, false), rot_own<true>(b1, a1, k1, false));
     }
 }
 template <> __device__ __forceinline__ void rot_halves<4>(u32x4& x, u32x4& y, const KCosSin* t, int32_t cs) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const KCosSin k = t[cs + i];
-        float a = __uint_as_float(x[i]), b = __uint_as_float(y[i]);
-        rot_pair<false>(a, b, k);
-        x[i] = __float_as_uint(a);
-        y[i] = __float_as_uint(b);
+        const float a = __uint_as_float(x[i]), b = __uint_as_float(y[i]);
+        x[i] = __float_as_uint(rot_own<false>(a, b, k, true));
+        y[i] = __float_as_uint(rot_own<false>(b, a, k, false));
     }
 }
 

@@ -1,7 +1,8 @@
 """Which half-split rows have their partner chunks exchanged between lanes: on the host the
 planner's choice (tests/lane_exchange_check.cpp), on the GPU rows that are neither whole wavefronts
-nor a divisor of one, against the oracle, with and without room for the ordered tiles' flags."""
+nor a divisor of one, against the oracle, with and without a workspace for the ordered tiles."""
 
+import ctypes
 import os
 import random
 import shutil
@@ -11,6 +12,7 @@ import pytest
 import torch
 
 import workloads as W
+from tests.parity_util import bits
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -50,13 +52,14 @@ def test_ragged_half_split_rows(kind, dtype):
         planes, stubs = W.alloc_contig(wl, "cuda:0")
         pristine = [t.clone() for t in planes]
         new_len = TC._run_and_check(L, wl, planes, stubs, f"ragged {kind}/{dtype} n={n}")
-        # a workspace too small for the tiles' flags: the same rows without tiles
-        cache = L.make_cache(TC._specs(L, wl, pristine))
+        # no workspace, one that is misaligned, one too small for the tiles' flags: the same bits without tiles
         dd = L.make_directives(TC._dir_dicts(wl, stubs))
-        small = torch.empty(256, dtype=torch.uint8, device="cuda:0")
-        assert L.leyline_splice_contig(cache, n, dd, len(dirs), workspace=small) == new_len
-        # one storage step, or 2e-6 of a pair's norm (below 10 here) where it nearly cancels: the two
-        # unit layouts may contract the pair's products in another order
-        for a, b in zip(planes, pristine):
-            torch.testing.assert_close(a[:, :new_len], b[:, :new_len], rtol=2.0 ** (-7 if dtype == "bf16" else -22),
-                                       atol=2e-5, msg=f"{kind}/{dtype} n={n}: with and without tiles")
+        buf = torch.empty(1 << 20, dtype=torch.uint8, device="cuda:0")
+        for ptr, size in ((None, 0), (buf.data_ptr() + 128, 1 << 19), (buf.data_ptr(), 256)):
+            other, got = [t.clone() for t in pristine], ctypes.c_int64(0)
+            cache = L.make_cache(TC._specs(L, wl, other))
+            assert L._lib.leyline_splice_contig(ctypes.byref(cache), n, dd, len(dirs), ctypes.byref(got), None, ptr, size,
+                                                L._stream(None)) == 0
+            assert got.value == new_len
+            for a, b in zip(planes, other):
+                assert torch.equal(bits(a[:, :new_len]), bits(b[:, :new_len])), f"{kind}/{dtype} n={n} workspace {size}"
