@@ -163,7 +163,8 @@ const char* leyline_last_hip_error(void);
  * Host-only check of a contiguous splice: validates exactly as leyline_splice_contig does and
  * reports (host outputs, each nullable) the new length, the number of kernel launches the splice
  * will enqueue, how many of them are ordered-tile launches, and the device workspace it needs in
- * bytes (0 when the splice runs without ordered tiles).  Enqueues nothing.
+ * bytes (0 when the splice runs without ordered tiles).  The counts are those of a call that brings
+ * this workspace.  Enqueues nothing.
  */
 int leyline_contig_query(const leyline_cache* cache, int64_t seq_len,
                          const leyline_directive* dirs, int32_t n_dirs,
@@ -189,6 +190,11 @@ int leyline_contig_query(const leyline_cache* cache, int64_t seq_len,
  * call's cos/sin table.  The call writes it on `stream` before use; reuse it only after the
  * stream has passed this call, and do not share one workspace between calls that may run at the
  * same time.
+ * A cache with a half-split rotary plane whose rows are neither a multiple nor a divisor of 1 KiB
+ * (MLA rows of 576 bf16 elements, 5 or 10 heads of 128) also runs without one: given NULL, or a
+ * workspace that is misaligned or smaller than the reported size, the call is made in rounds or
+ * ordered chains instead of ordered tiles, with the same result bit for bit, and touches no
+ * workspace.  Small shifts then take up to 1.6 times as long.
  * device_status: device int32, nullable.  A tile waits for the tiles whose source rows its
  * destination overlaps; each wait is bounded (a few hundred milliseconds at least, where a
  * correct schedule waits microseconds).  A tile that gives up ORs LEYLINE_STATUS_TILE_TIMEOUT
@@ -199,7 +205,7 @@ int leyline_contig_query(const leyline_cache* cache, int64_t seq_len,
  * filled by a kernel), so the call may be captured into a HIP graph; each replay repeats the same
  * splice.
  * Errors: E_INVAL, E_RANGE, E_ORDER, E_OVERLAP, E_CAPACITY (new length > capacity), E_MODE,
- * E_WORKSPACE (missing, misaligned or too small), E_HIP.
+ * E_WORKSPACE (missing, misaligned or too small, except on the caches above), E_HIP.
  */
 int leyline_splice_contig(const leyline_cache* cache, int64_t seq_len,
                           const leyline_directive* dirs, int32_t n_dirs,

@@ -202,6 +202,21 @@ def test_contig_tiles_need_a_workspace():
                                         0x10000, 16, None) == L.E_WORKSPACE        # too small
 
 
+def test_more_tiles_than_a_launch_numbers():
+    """One-token shifts whose ordered tiles exceed 31-bit ticket numbers: ragged half-split rows, which
+    also run without tiles, are planned as ordered chains; other rows are refused."""
+    import torch
+    layers, rows = 65535, 4 << 20                              # 36,864 tiles of 8192 chunks per layer
+    t = _FakeTensor((layers, rows, 576), torch.bfloat16)
+    d = _dirs([(10, 11, 0)])
+    half = L.make_cache([L.PlaneSpec(t, 1, 576, 512, 64, L.ROPE_NEOX, 1e4)])
+    q = L.leyline_contig_query(half, rows, d, 1)
+    assert (q.new_len, q.launches, q.tile_launches, q.workspace_bytes) == (rows - 1, 1, 0, 0)
+    with pytest.raises(L.LeylineError) as e:
+        L.leyline_contig_query(L.make_cache([L.PlaneSpec(t, 1, 576, 512, 64, L.ROPE_INTERLEAVED, 1e4)]), rows, d, 1)
+    assert e.value.code == L.E_INVAL
+
+
 def test_noalloc_splice_refuses_more_than_its_scratch_before_any_enqueue():
     """leyline_splice_contig_noalloc takes its workspace from a fixed 1 MiB array: a small-shift
     splice whose ordered tiles need more (here 61 layers of a 600K-token MLA cache: one 4-byte
