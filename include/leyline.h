@@ -298,13 +298,14 @@ int leyline_paged_plan(int32_t page_size, int32_t n_seqs, const int32_t* seq_len
  * plan (runs of pages, per-sequence and per-directive tables and cos/sin; plans of at most 2560
  * bytes travel in the kernel arguments instead, larger ones are uploaded with an asynchronous
  * copy on `stream`) and, when the call assembles more than 1024 rows, room for the row table that a
- * kernel of a large call writes from it (24 bytes per row of every ASSEMBLE page, 4 bytes per fresh page);
- * when some plane rotates at least 1 KiB per row and at least 64 pages are re-used, the REMAP
- * pages resolved and sorted by physical page (16 bytes per REMAP page);
- * reuse it only after the stream has passed this call.  Any page_size whose rows keep the
- * 16-byte alignment is accepted.  A call with a plan of at most 2560 bytes enqueues kernels only
- * (a single one up to some hundreds of MB moved); an uploaded plan comes from host memory the
- * call owns only while it runs: do not capture such a call into a HIP graph.
+ * kernel of a large call, or of one of many short edits, writes from it (24 bytes per row of every
+ * ASSEMBLE page, 4 bytes per fresh page); when some plane rotates at least 1 KiB per row and at least
+ * 64 pages are re-used, room for the REMAP pages resolved and sorted by physical page (16 bytes per
+ * REMAP page; written by calls that rotate at least 512 MiB, read and written); reuse it only after
+ * the stream has passed this call.  Any page_size whose rows keep the 16-byte alignment is accepted.
+ * A call with a plan of at most 2560 bytes enqueues kernels only (a single one for most calls that
+ * gather less than 640 MiB and rotate less than 512 MiB, read and written); an uploaded plan comes
+ * from host memory the call owns only while it runs: do not capture such a call into a HIP graph.
  *
  * flags: 0, or LEYLINE_PAGED_COPY_ON_WRITE (no REMAP pages: no old page is written).
  * Ownership: only ASSEMBLE pages (fresh) and REMAP pages (rotary bands, in place) are written.

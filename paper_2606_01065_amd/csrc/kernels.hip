@@ -70,17 +70,9 @@ constexpr int CRPT = LEYLINE_CONTIG_RPT;   // rows per thread of a rotating roun
 // 32K splice 613 / 576 us.  The kernel and the launcher's grid both take it from here.
 LEYLINE_HD inline int round_rows_per_thread(bool rotates) { return rotates ? CRPT : 1; }
 constexpr int MOVE_TPB = LEYLINE_MOVE_TPB; // its workgroup size
-#ifndef LEYLINE_PAGED_TPB
-#define LEYLINE_PAGED_TPB 256
-#endif
 #ifndef LEYLINE_GATHER_SPLIT_PAGE
 #define LEYLINE_GATHER_SPLIT_PAGE 4    // smallest page size whose gather is split by XCD
 #endif
-#ifndef LEYLINE_PAGED_LPT
-#define LEYLINE_PAGED_LPT 2
-#endif
-constexpr int PAGED_TPB = LEYLINE_PAGED_TPB;   // paged gather workgroup size
-constexpr int PAGED_LPT = LEYLINE_PAGED_LPT;   // layers per paged-gather thread
 constexpr int WIN = LEYLINE_WIN;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -969,14 +961,14 @@ __global__ __launch_bounds__(PAGED_TPB) void rotate_rows_kernel(const KRotatePar
 // kernel (rows laid end to end, one 16-byte chunk per thread, so a wavefront reads one row entry
 // and moves whole lines); its last blocks rotate the rotary bands of REMAP pages (re-used whole
 // pages) in place, each looking its pages up in the plan and the old block table (or reading
-// them from paged_remap_order_kernel's physical-order list).  The rows of a gather of up to
-// KORDER_BYTES are resolved by the gathering blocks themselves, and the new block tables and freed
-// list are written by blocks between the two: one launch per call.  A larger gather first runs
-// paged_resolve_kernel, which expands the page runs once for all layers
+// them from paged_remap_order_kernel's physical-order list).  The rows of most gathers are resolved
+// by the gathering blocks themselves, and the new block tables and freed list are written by blocks
+// between the two: one launch per call.  A gather of more than KORDER_BYTES, or of many short spans
+// (gather_row_table), first runs paged_resolve_kernel, which expands the page runs once for all layers
 // and planes into a row table (for every row of every ASSEMBLE page: which old physical page and
 // row, or which replacement token, it comes from, which fresh page it goes to, which shift
-// re-anchors it) and writes the block tables and the freed list; paged_order_kernel before it
-// lays the row table out in destination-page order.
+// re-anchors it) and writes the block tables and the freed list; paged_order_kernel before it lays
+// the row table of at least KORDER_MIN pages out in destination-page order.
 // Nothing is written to an old page except the rotary bands of REMAP pages, which no ASSEMBLE
 // row reads.
 
@@ -2034,10 +2026,7 @@ extern "C" int leyline_splice_paged(const leyline_cache* cache, int32_t n_seqs, 
         if (int64_t(t.n_rows) * planes[p].tpr > INT32_MAX - 1024) return LEYLINE_E_INVAL;
         if (int64_t(t.n_remap) * cache->page_size * planes[p].rot_tpr > INT32_MAX - 1024) return LEYLINE_E_INVAL;
     }
-    int64_t row_bytes = 0;
-    for (int p = 0; p < n_planes; ++p) row_bytes += planes[p].row_bytes;
-    const bool row_table = t.n_rows > KINLINE_ROWS && t.n_asm >= KORDER_MIN &&
-                           2 * row_bytes * t.n_rows * cache->n_layers >= KORDER_BYTES;
+    const bool row_table = gather_row_table(planes, n_planes, t, cache->n_layers);
     if (t.upload > INT32_MAX) return LEYLINE_E_INVAL;
     const bool inline_plan = t.upload <= KPLAN_INLINE;
     if (!inline_plan) {
@@ -2103,12 +2092,14 @@ extern "C" int leyline_splice_paged(const leyline_cache* cache, int32_t n_seqs, 
         const bool bf16 = cache->dtype == LEYLINE_BF16;
         const unsigned layer_groups = unsigned((cache->n_layers + PAGED_LPT - 1) / PAGED_LPT);
         if (row_table) {
-            int32_t shift = 0;
-            while (((cache->capacity - 1) >> shift) >= KORDER_BUCKETS) ++shift;
-            P.order_shift = shift;
-            P.order = reinterpret_cast<int32_t*>(ws + t.off_order);
-            rc = launch(paged_order_kernel, dim3(1), s, P, ORDER_TPB);
-            if (rc) return rc;
+            if (t.n_asm >= KORDER_MIN) {
+                int32_t shift = 0;
+                while (((cache->capacity - 1) >> shift) >= KORDER_BUCKETS) ++shift;
+                P.order_shift = shift;
+                P.order = reinterpret_cast<int32_t*>(ws + t.off_order);
+                rc = launch(paged_order_kernel, dim3(1), s, P, ORDER_TPB);
+                if (rc) return rc;
+            }
             rc = launch(paged_resolve_kernel, dim3(unsigned((int64_t(t.n_rows) + n_tables + TPB - 1) / TPB)), s, P);
             if (rc) return rc;
         } else {

@@ -386,6 +386,16 @@ struct KPagedTables {
     int32_t remap_sorted;    // 1: the REMAP pages are laid out in physical order at off_remap_sorted
 };
 
+// Workgroup size of the paged data kernel, and the consecutive layers each of its threads moves.
+#ifndef LEYLINE_PAGED_TPB
+#define LEYLINE_PAGED_TPB 256
+#endif
+#ifndef LEYLINE_PAGED_LPT
+#define LEYLINE_PAGED_LPT 2
+#endif
+constexpr int PAGED_TPB = LEYLINE_PAGED_TPB;
+constexpr int PAGED_LPT = LEYLINE_PAGED_LPT;
+
 // Plans of at most this many bytes travel in the kernel arguments instead of being uploaded.
 constexpr int32_t KPLAN_INLINE = 2560;
 
@@ -442,25 +452,33 @@ struct KPagedParams {
     alignas(16) unsigned char blob[KPLAN_INLINE];
 };
 
-// Gathers.  A call that assembles more than KINLINE_ROWS rows in at least KORDER_MIN pages and
-// moves at least KORDER_BYTES (read and written) runs in destination-page order (neighbouring
-// physical pages processed together), from a row table written by two launches before the data
-// launch; every other call is one launch whose workgroups resolve their rows from the plan in plan
-// order.  The order is worth 3-5% of a large gather's time and costs 8-14 us.  Row table in
-// destination order / one launch, 61-layer MLA cache: 64-token pages 111 MB 32.5 / 25 us,
-// 374 MB 79.5 / 75.4, 845 MB 163 / 162, 1.85 GB 330 / 338, 12.6 GB 2190 / 2318; 16-token pages 843 MB
-// 165 / 168; token slots 842 MB 156 / 153, 1.85 GB 335 / 346.  KORDER_BUCKETS: buckets of pages,
-// counted in LDS.
+// Gathers.  A call runs from a row table, written by two launches before the data launch, in
+// destination-page order (neighbouring physical pages processed together; from KORDER_MIN pages on),
+// or in one launch whose workgroups resolve their rows from the plan in plan order.  Up to
+// KINLINE_ROWS rows it is one launch; above, it takes the table
+//  - for its order, when it moves at least KORDER_BYTES (read and written) in at least KORDER_MIN
+//    pages: the order is worth 2-6% of a gather beyond 1 GB and costs 8-14 us.  61-layer MLA cache, row
+//    table / one launch: 64-token pages 111 MB 32.5 / 25 us, 374 MB 79.5 / 75.4, 845 MB 163 / 162,
+//    1.85 GB 330 / 338, 12.6 GB 2190 / 2318; 16-token pages 843 MB 165 / 168; token slots 842 MB
+//    156 / 153, 1.85 GB 335 / 346: level between 0.4 and 0.9 GB, hence the bound;
+//  - when many workgroups lie across spans (rows of one page run and one segment): each of them
+//    resolves its rows lane by lane, again in every layer group, which takes the chip about 1.8 ns
+//    (2.7 in packed blocks) against 9 us for the table (gather_row_table).  Copy-on-write token slots
+//    of many short spans, row table / one launch: MLA 61 layers, 4,000 rows in spans of 3 119 / 215 us,
+//    of 24 115 / 142; 16 layers, 1,100 rows in spans of 3 22.8 / 21.9; 8 GQA heads, 16 layers, 4,000
+//    rows in spans of 3 109 / 138, of 24 105 / 104; 64 sequences of 64 tokens, 61-layer MLA, one edit
+//    each 76 / 99; 32 of 200 tokens, 16 layers 36 / 33.
+// KORDER_BUCKETS: buckets of pages, counted in LDS.
 constexpr int32_t KINLINE_ROWS = 1024;
 constexpr int32_t KORDER_MIN = 64;
 constexpr int64_t KORDER_BYTES = int64_t(640) << 20;
 constexpr int32_t KORDER_BUCKETS = 4096;
+constexpr int64_t KTABLE_NS = 9000;
 
-// A gather whose spans (rows of one page run and one segment) are shorter than KSPAN_ROWS on average:
-// hardly any of its workgroups lies in one span, so a plane that has no shift to look up skips the
-// search for it.  27-layer split MLA token slots, 256 replacements of 3 rows: 53.6 us without the
-// search, 57.3 with it; a 61-layer copy-on-write gather of 8-row spans takes 59.3 us with it, 71.7
-// when every lane searches by itself.
+// A one-launch gather whose spans are shorter than KSPAN_ROWS on average: hardly any of its workgroups
+// lies in one span, so a plane that has no shift to look up skips the search for it.  27-layer split
+// MLA token slots, 256 replacements of 3 rows: 53.6 us without the search, 57.3 with it; a 61-layer
+// copy-on-write gather of 8-row spans takes 59.3 us with it, 71.7 when every lane searches by itself.
 constexpr int32_t KSPAN_ROWS = 4;
 LEYLINE_HD inline bool short_gather_spans(int64_t n_rows, int64_t n_spans) { return n_rows < KSPAN_ROWS * n_spans; }
 

@@ -648,6 +648,21 @@ int plan_paged(int32_t page_size, int32_t n_seqs, const int32_t* seq_lens,
     return LEYLINE_OK;
 }
 
+bool gather_row_table(const KPlane* planes, int n_planes, const KPagedTables& t, int32_t n_layers) {
+    if (t.n_rows <= KINLINE_ROWS) return false;
+    int64_t row_bytes = 0, across_ns10 = 0;              // tenths of a nanosecond, per layer group
+    for (int p = 0; p < n_planes; ++p) {
+        const KPlane& pl = planes[p];
+        row_bytes += pl.row_bytes;
+        // a packed block is taken by several workgroups, each of which covers all of its rows
+        const int64_t each = pl.pack_groups ? 1 + int64_t(pl.pack_groups) * pl.tpr / PAGED_TPB : 1;
+        const int64_t groups = (int64_t(t.n_rows) * pl.tpr + PAGED_TPB - 1) / PAGED_TPB;
+        across_ns10 += (pl.pack_groups ? 27 : 18) * std::min(groups, each * t.n_spans);
+    }
+    if (t.n_asm >= KORDER_MIN && 2 * row_bytes * t.n_rows * n_layers >= KORDER_BYTES) return true;
+    return across_ns10 * ((n_layers + PAGED_LPT - 1) / PAGED_LPT) >= 10 * KTABLE_NS;
+}
+
 int build_paged_image(const leyline_cache* cache, const PagedPlan& plan, int32_t n_seqs,
                       const leyline_directive* dirs, int32_t n_dirs, int32_t bt_stride,
                       PagedImage* img) {

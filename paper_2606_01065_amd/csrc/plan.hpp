@@ -138,4 +138,7 @@ int build_paged_image(const leyline_cache* cache, const PagedPlan& plan, int32_t
                       const leyline_directive* dirs, int32_t n_dirs, int32_t bt_stride,
                       PagedImage* img);
 
+// Whether the call's gather runs from a row table (large, or many short spans) or in one launch.
+bool gather_row_table(const KPlane* planes, int n_planes, const KPagedTables& t, int32_t n_layers);
+
 }  // namespace leyline

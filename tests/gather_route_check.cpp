@@ -2,7 +2,7 @@
 // one call after the other:
 //   dtype layers page flags planes, then per plane: row heads head_stride rot_offset rot_dim style
 //   sequences, then their lengths; directives, then per directive: sequence start end replacement
-// Prints per call "<gathered rows> <fresh pages> <spans> <short spans>".
+// Prints per call "<gathered rows> <fresh pages> <spans> <short spans> <row table>".
 #include <cstdio>
 #include <vector>
 
@@ -52,7 +52,8 @@ int main() {
             build_paged_image(&cache, plan, n_seqs, plan.dirs, n_dirs, 1 << 24, &img) != LEYLINE_OK)
             return 2;
         const KPagedTables& t = img.tables;
-        std::printf("%d %d %d %d\n", t.n_rows, t.n_asm, t.n_spans, short_gather_spans(t.n_rows, t.n_spans) ? 1 : 0);
+        std::printf("%d %d %d %d %d\n", t.n_rows, t.n_asm, t.n_spans, short_gather_spans(t.n_rows, t.n_spans) ? 1 : 0,
+                    gather_row_table(planes, n_planes, t, cache.n_layers) ? 1 : 0);
     }
     return 0;
 }

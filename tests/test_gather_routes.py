@@ -76,6 +76,33 @@ def random_call(rng, page):
 def test_spans_of_a_gather(ask):
     rng = random.Random(5)
     calls = [(random_call(rng, page), cow) for page in (1, 3, 16) for cow in (0, 1) for _ in range(60)]
-    for (wl, cow), (rows, pages, spans, short) in zip(calls, ask(calls)):
+    for (wl, cow), (rows, pages, spans, short, _) in zip(calls, ask(calls)):
         assert (rows, pages, spans) == counts(wl, cow), (wl.page_size, cow, wl.seq_lens, wl.dirs)
         assert short == (rows < 4 * spans)
+
+
+def turned_spans(rows, k):
+    """Copy-on-write token slots: every row moves by one place, spans of k replacement rows and k old rows in turn."""
+    dirs = [W.Dir(5 + 2 * k * i, 5 + 2 * k * i + k, k + (i == 0)) for i in range(rows // (2 * k))]
+    return dirs, [5 + 2 * k * len(dirs)]
+
+
+def one_edit_each(seqs, tokens):
+    return [W.Dir(tokens // 4, tokens // 4 + 7, 11, seq=b) for b in range(seqs)], [tokens] * seqs
+
+
+MLA, GQA8 = [W.mla_plane()], W.gqa_planes(heads=8, dim=128)
+
+
+@pytest.mark.parametrize("planes,layers,page,call,table", [
+    (MLA, 61, 1, turned_spans(4000, 3), 1), (MLA, 61, 1, turned_spans(4000, 24), 1), (MLA, 16, 1, turned_spans(1100, 3), 0),
+    (MLA, 16, 1, turned_spans(4000, 3), 1), (MLA, 2, 1, turned_spans(4000, 3), 0), (MLA, 2, 1, turned_spans(12000, 3), 1),
+    (MLA, 61, 1, turned_spans(1000, 3), 0), (W.mla_split_planes(), 2, 1, turned_spans(12000, 3), 0),
+    (GQA8, 16, 1, turned_spans(4000, 3), 1), (GQA8, 16, 1, turned_spans(4000, 24), 0), (GQA8, 4, 1, turned_spans(1100, 3), 0),
+    (MLA, 61, 16, one_edit_each(64, 64), 1), (MLA, 16, 16, one_edit_each(32, 200), 0), (MLA, 16, 64, one_edit_each(128, 100), 1),
+    (MLA, 61, 64, ([W.Dir(100, 160, 44)], [3000]), 0), (MLA, 61, 64, ([W.Dir(100, 160, 44)], [6000]), 1)])
+def test_row_table_or_one_launch(ask, planes, layers, page, call, table):
+    """Calls whose two routes were timed: each takes the faster one (the last two differ in bytes alone)."""
+    dirs, lens = call
+    (rows, pages, spans, _, got), = ask([(W.Workload("route", layers, "bf16", planes, dirs, lens, page_size=page), 1)])
+    assert got == table, (rows, pages, spans)

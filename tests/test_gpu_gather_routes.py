@@ -110,3 +110,41 @@ def test_many_short_spans(kind, dtype):
         for pi, plane in enumerate(planes):
             assert_rows_match(host(pools[pi]).reshape(want[pi].shape), want[pi], plane, dtype,
                               what=f"short spans {kind} page={page} plane {pi}")
+
+
+@pytest.mark.parametrize("kind,page,dtype", [("mla", 1, "bf16"), ("mla", 3, "f32"), ("mla", 64, "bf16"), ("mla_half", 1, "bf16"),
+                                             ("gqa8", 1, "bf16"), ("heads96", 16, "bf16"), ("heads96", 64, "f32")])
+def test_short_spans_in_a_row_table(kind, page, dtype):
+    """More than 1,024 rows in short spans over many layers: resolved once into a row table (without an order
+    of its pages below 64 pages).  Every layer holds the same rows, as in test_both_routes."""
+    from paper_2606_01065_amd import leyline as L
+    rng, dirs, at, layers = random.Random(f"{kind}/{page}"), [], 3, 61
+    for _ in range(400):
+        e = at + rng.randint(0, 3)
+        dirs.append(W.Dir(at, e, rng.randint(0, 3)))
+        at = e + rng.choice([1, 2, 5, 9])
+    wl = W.Workload(f"table_{kind}", 1, dtype, SHORT_KINDS[kind], dirs, [at], page_size=page, seed=page)
+    plans = O.plan_paged(wl.seq_lens, TP._odirs(wl), page, remap=False)
+    fresh = sum(k == O.ASSEMBLE for p in plans for k in p.kinds)
+    assert fresh * page > 1024 and (fresh < 64) == (page == 64), fresh
+    print(f"[case] row table {kind}/{dtype} page={page} rows={fresh * page} spans of {len(dirs)} edits", flush=True)
+    pools1, bt, free, stubs1 = W.alloc_paged(wl, "cuda:0", spare_pages=fresh + 3)
+    before, bt_h, free_h = [host(p) for p in pools1], host(bt), host(free)
+    stubs_h = [[host(s).reshape(1, s.shape[1], p.row_elems) for s, p in zip(per, wl.planes)] for per in stubs1]
+    wl.n_layers = layers
+    pools = [p.expand(layers, *p.shape[1:]).contiguous() for p in pools1]
+    stubs = [[s.expand(layers, *s.shape[1:]).contiguous() for s in per] for per in stubs1]
+    bt_out, freed, new_lens, ws = TP._run_gpu(L, wl, pools, bt, free, stubs, flags=1, ws_fill=0x5a)
+    table = ws[-(24 * fresh * page + (4 * fresh if fresh >= 64 else 0)):]      # the end of the workspace
+    assert not bool((table == 0x5a).all()), "no row table was written"
+    planes = [oracle_plane(p) for p in wl.planes]
+    flat = [b.reshape(b.shape[0], b.shape[1], b.shape[2], -1) for b in before]
+    want, want_bt, want_lens, want_freed = O.splice_paged(flat, planes, dtype, bt_h, wl.seq_lens, TP._odirs(wl), stubs_h,
+                                                          list(free_h), page, remap=False)
+    assert new_lens == want_lens
+    assert np.array_equal(host(bt_out), want_bt)
+    assert list(host(freed)) == want_freed
+    for pi, plane in enumerate(planes):
+        assert_rows_match(host(pools[pi][:1]).reshape(want[pi].shape), want[pi], plane, dtype,
+                          what=f"row table {kind} page={page} plane {pi}")
+        assert torch.equal(pools[pi], pools[pi][:1].expand_as(pools[pi])), "layers differ"

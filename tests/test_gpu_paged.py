@@ -24,7 +24,9 @@ def L():
     return leyline
 
 
-def _run_gpu(L, wl, pools, bt, free, stubs, flags=0):
+def _run_gpu(L, wl, pools, bt, free, stubs, flags=0, ws_fill=None):
+    """(new block tables, freed list, new lengths) of a checked call, and its workspace where ws_fill says
+    what byte it holds before."""
     specs = [L.PlaneSpec(t, p.n_heads, p.head_stride or p.row_elems, p.rot_offset, p.rot_dim,
                          p.style, p.base) for p, t in zip(wl.planes, pools)]
     cache = L.make_cache(specs, paged=True)
@@ -36,6 +38,8 @@ def _run_gpu(L, wl, pools, bt, free, stubs, flags=0):
     bt_out = torch.full_like(bt, -7)
     freed = torch.full((max(1, n_freed),), -7, dtype=torch.int32, device=DEV)
     ws = torch.empty(max(256, ws_bytes), dtype=torch.uint8, device=DEV)
+    if ws_fill is not None:
+        ws.fill_(ws_fill)
     status = torch.zeros(1, dtype=torch.int32, device=DEV)
     got_lens, got_fresh, got_freed = L.leyline_splice_paged(cache, wl.seq_lens, bt, bt_out, dirs,
                                                             len(wl.dirs), free, freed, ws,
@@ -43,6 +47,8 @@ def _run_gpu(L, wl, pools, bt, free, stubs, flags=0):
     torch.cuda.synchronize()
     assert (got_lens, got_fresh, got_freed) == (new_lens, fresh, n_freed)
     assert int(status.item()) == 0
+    if ws_fill is not None:
+        return bt_out, freed[:n_freed], new_lens, ws
     return bt_out, freed[:n_freed], new_lens
 
 
