@@ -219,46 +219,48 @@ template <> __device__ __forceinline__ void rot_interleaved<4>(u32x4& v, const K
 
 // Half-split chunks: element e of the low-half chunk `x` pairs with element e of the high-half
 // chunk `y`; EPC pairs with cos/sin table[cs + e].  Both chunks are updated.
-template <int ESZ> __device__ __forceinline__ void rot_halves(u32x4& x, u32x4& y, const KCosSin* t, int32_t cs);
-template <> __device__ __forceinline__ void rot_halves<2>(u32x4& x, u32x4& y, const KCosSin* t, int32_t cs) {
+// VIA_FLOAT: fp64 results go to bf16 through the nearest-even float, else rounded to odd (the same bits).
+template <int ESZ, bool VIA_FLOAT = true>
+__device__ __forceinline__ void rot_halves(u32x4& x, u32x4& y, const KCosSin* t, int32_t cs) {
+    if constexpr (ESZ == 2) {
 #if LEYLINE_PAIR_F64
-    {
+        if constexpr (VIA_FLOAT) {
 #pragma clang fp contract(off)
-        u16x2 mid{0xffff, 0xffff};
-        u32x4 r, q;
+            u16x2 mid{0xffff, 0xffff};
+            u32x4 r, q;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const KCosSin k0 = t[cs + 2 * i], k1 = t[cs + 2 * i + 1];
+                const double a0 = bf_lo(x[i]), a1 = bf_hi(x[i]), b0 = bf_lo(y[i]), b1 = bf_hi(y[i]);
+                r[i] = pack_bf16_f64(a0 * k0.c - b0 * k0.s, a1 * k1.c - b1 * k1.s, mid);
+                q[i] = pack_bf16_f64(a0 * k0.s + b0 * k0.c, a1 * k1.s + b1 * k1.c, mid);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (!any_between(mid)) {
+                x = r;
+                y = q;
+                return;
+            }
+            again(x, cs);
+            again(y, cs);
+        }
+#endif
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const KCosSin k0 = t[cs + 2 * i], k1 = t[cs + 2 * i + 1];
-            const double a0 = bf_lo(x[i]), a1 = bf_hi(x[i]), b0 = bf_lo(y[i]), b1 = bf_hi(y[i]);
-            r[i] = pack_bf16_f64(a0 * k0.c - b0 * k0.s, a1 * k1.c - b1 * k1.s, mid);
-            q[i] = pack_bf16_f64(a0 * k0.s + b0 * k0.c, a1 * k1.s + b1 * k1.c, mid);
-            __builtin_amdgcn_sched_barrier(0);
+            const float a0 = bf_lo(x[i]), a1 = bf_hi(x[i]);
+            const float b0 = bf_lo(y[i]), b1 = bf_hi(y[i]);
+            x[i] = pack_bf16(rot_own<true>(a0, b0, k0, true), rot_own<true>(a1, b1, k1, true));
+            y[i] = pack_bf16(rot_own<true>(b0, a0, k0, false), rot_own<true>(b1, a1, k1, false));
         }
-        if (!any_between(mid)) {
-            x = r;
-            y = q;
-            return;
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const KCosSin k = t[cs + i];
+            const float a = __uint_as_float(x[i]), b = __uint_as_float(y[i]);
+            x[i] = __float_as_uint(rot_own<false>(a, b, k, true));
+            y[i] = __float_as_uint(rot_own<false>(b, a, k, false));
         }
-        again(x, cs);
-        again(y, cs);
-    }
-#endif
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const KCosSin k0 = t[cs + 2 * i], k1 = t[cs + 2 * i + 1];
-        const float a0 = bf_lo(x[i]), a1 = bf_hi(x[i]);
-        const float b0 = bf_lo(y[i]), b1 = bf_hi(y[i]);
-        x[i] = pack_bf16(rot_own<true>(a0, b0, k0, true), rot_own<true>(a1, b1, k1, true));
-        y[i] = pack_bf16(rot_own<true>(b0, a0, k0, false), rot_own<true>(b1, a1, k1, false));
-    }
-}
-template <> __device__ __forceinline__ void rot_halves<4>(u32x4& x, u32x4& y, const KCosSin* t, int32_t cs) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const KCosSin k = t[cs + i];
-        const float a = __uint_as_float(x[i]), b = __uint_as_float(y[i]);
-        x[i] = __float_as_uint(rot_own<false>(a, b, k, true));
-        y[i] = __float_as_uint(rot_own<false>(b, a, k, false));
     }
 }
 
@@ -391,7 +393,7 @@ __device__ __forceinline__ void rotate_chunk(const KPlane& pl, u32x4& v, int32_t
 
 // Row kernels: move unit u of one row from src to dst, re-anchored with the cos/sin block
 // table[cs + pair] (cs < 0: copied unchanged).
-template <int ESZ>
+template <int ESZ, bool VIA_FLOAT = true>
 __device__ __forceinline__ void move_row_unit(const KPlane& pl, const char* src, char* dst, int32_t u,
                                               const KCosSin* table, int32_t cs) {
     if (pl.rot == KROT_NEOX && !pl.neox_lanes) {
@@ -399,7 +401,7 @@ __device__ __forceinline__ void move_row_unit(const KPlane& pl, const char* src,
         const int64_t a = int64_t(un.a) * 16, b = int64_t(un.b) * 16;
         u32x4 x = ld16(src + a), y;
         if (un.b >= 0) y = ld16(src + b);
-        if (cs >= 0 && un.kind == KROT_NEOX) rot_halves<ESZ>(x, y, table, cs + un.pair);
+        if (cs >= 0 && un.kind == KROT_NEOX) rot_halves<ESZ, VIA_FLOAT>(x, y, table, cs + un.pair);
         st16(dst + a, x);
         if (un.b >= 0) st16(dst + b, y);
         return;
@@ -479,7 +481,7 @@ __device__ __forceinline__ void band_load(const BandPos& p, const char* row, int
     }
 }
 
-template <int ESZ>
+template <int ESZ, bool VIA_FLOAT = true>
 __device__ __forceinline__ void band_rotate_store(const KPlane& pl, const BandPos& p, char* row,
                                                   int64_t lstride, int nl, u32x4 (&x)[PAGED_LPT],
                                                   u32x4 (&y)[PAGED_LPT], const KCosSin* table, int32_t cs) {
@@ -488,7 +490,7 @@ __device__ __forceinline__ void band_rotate_store(const KPlane& pl, const BandPo
     for (int l = 0; l < PAGED_LPT; ++l) {
         if (l < nl) {
             if (p.two) {
-                rot_halves<ESZ>(x[l], y[l], table, cs + p.j * EPC);
+                rot_halves<ESZ, VIA_FLOAT>(x[l], y[l], table, cs + p.j * EPC);
                 st16(row + l * lstride + p.b, y[l]);
             } else {
                 rotate_band_chunk<ESZ>(pl, x[l], p.j, table, cs);
@@ -1369,7 +1371,7 @@ __global__ __launch_bounds__(TPB) void paged_resolve_kernel(const KPagedParams P
 
 // One workgroup of the ASSEMBLE gather (bx: its index among the gather's workgroups).  INLINE:
 // the rows are resolved here from the plan instead of read from the row table.
-template <int ESZ, bool INLINE>
+template <int ESZ, bool INLINE, bool TWO>
 __device__ __forceinline__ void paged_move_block(const KPagedParams& P, const PlanView& V, int plane, int32_t bx,
                                                  int32_t lgroup, KCosSin* lcs) {
     const KPlane& pl = P.planes[plane];
@@ -1422,7 +1424,7 @@ __device__ __forceinline__ void paged_move_block(const KPagedParams& P, const Pl
     if (pl.rot == KROT_NEOX && !pl.neox_lanes) {        // two-chunk units (rare layouts)
         if (active)
             for (int l = 0; l < nl; ++l)
-                move_row_unit<ESZ>(pl, src + l * src_step, dst + l * pl.layer_stride, u, V.cs, cs);
+                move_row_unit<ESZ, !TWO>(pl, src + l * src_step, dst + l * pl.layer_stride, u, V.cs, cs);
         return;
     }
     const int64_t off = int64_t(u) * 16;
@@ -1452,7 +1454,7 @@ __device__ __forceinline__ void paged_move_block(const KPagedParams& P, const Pl
 // to end, PAGED_LPT layers per thread, rotated in place.  The workgroup stages the cos/sin block
 // of its first page's shift in LDS; rows with another shift (where runs meet) read the plan's
 // table.
-template <int ESZ>
+template <int ESZ, bool TWO>
 __device__ __forceinline__ void paged_remap_block(const KPagedParams& P, const PlanView& V, int plane, int32_t bx,
                                                   int32_t lgroup, KCosSin* lcs) {
     const KPlane& pl = P.planes[plane];
@@ -1503,8 +1505,8 @@ __device__ __forceinline__ void paged_remap_block(const KPagedParams& P, const P
     cs_commit(lcs, c, cs0 >= 0 ? pl.n_pairs : 0);
     __syncthreads();
     if (!active) return;
-    if (e.cs == cs0) band_rotate_store<ESZ>(pl, bp, row, pl.layer_stride, nl, x, y, lcs, 0);
-    else band_rotate_store<ESZ>(pl, bp, row, pl.layer_stride, nl, x, y, V.cs, e.cs + pl.cs_off);
+    if (e.cs == cs0) band_rotate_store<ESZ, !TWO>(pl, bp, row, pl.layer_stride, nl, x, y, lcs, 0);
+    else band_rotate_store<ESZ, !TWO>(pl, bp, row, pl.layer_stride, nl, x, y, V.cs, e.cs + pl.cs_off);
 }
 
 // One dimension of workgroups: the gather workgroups of every layer group first (plane by plane
@@ -1514,9 +1516,15 @@ __device__ __forceinline__ void paged_remap_block(const KPagedParams& P, const P
 // splice (the REMAP rotation) follows; planes without work get no workgroups.  SOLO: only plane 0
 // has work in this launch, so no workgroup looks its plane up.  INLINE: the gather resolves its
 // rows (no row table) and the launch may carry table work.
-template <int ESZ, bool SOLO, bool INLINE>
+//
+// TWO (fp64 pairs, bf16): some plane moves or rotates two-chunk units.  Six wavefronts (80 registers
+// instead of 93) are worth 5-10% where single chunks rotate, but cost the two-chunk units, which hold
+// twice the data, 3%, and the rounding through floats another 2%: 3 heads of 96, 32 layers, the
+// 16-token pages behind an edit of a 16K cache rotated in place 139.9 us with both, 132.9 without.
+// fp32 rows hold half as many pairs a chunk and ran 2% slower under the limit (GQA gather 334 / 328 us).
+template <int ESZ, bool SOLO, bool INLINE, bool TWO>
 #if LEYLINE_PAIR_F64
-__attribute__((amdgpu_waves_per_eu(6)))   // 80 registers; 93 without the limit, one wavefront in six fewer
+__attribute__((amdgpu_waves_per_eu(ESZ == 2 && !TWO ? 6 : 1)))
 #endif
 __global__ __launch_bounds__(PAGED_TPB) void paged_data_kernel(const KPagedParams P) {
     __shared__ KCosSin lcs[KMAX_CS];
@@ -1528,7 +1536,7 @@ __global__ __launch_bounds__(PAGED_TPB) void paged_data_kernel(const KPagedParam
         const int32_t y = fdiv(b, P.move_blk_div);
         const int32_t bx = b - y * moves;
         const int p = SOLO ? 0 : plane_of(P.move_base, P.n_planes, bx);
-        paged_move_block<ESZ, INLINE>(P, V, p, bx - P.move_base[p], y, lcs);
+        paged_move_block<ESZ, INLINE, TWO>(P, V, p, bx - P.move_base[p], y, lcs);
         return;
     }
     b -= moves * P.layer_groups;
@@ -1543,7 +1551,7 @@ __global__ __launch_bounds__(PAGED_TPB) void paged_data_kernel(const KPagedParam
     const int32_t y = fdiv(b, P.remap_blk_div);
     const int32_t bx = b - y * remaps;
     const int p = SOLO ? 0 : plane_of(P.remap_base, P.n_planes, bx);
-    paged_remap_block<ESZ>(P, V, p, bx - P.remap_base[p], y, lcs);
+    paged_remap_block<ESZ, TWO>(P, V, p, bx - P.remap_base[p], y, lcs);
 }
 
 // -------------------------------------------------------------------------- host launchers ---
@@ -1962,13 +1970,19 @@ extern "C" int leyline_rotate_delta(const leyline_cache* cache, int64_t delta,
 }
 
 // The paged data kernel variant for (dtype, one plane only, inline rows).
-static int launch_paged_data(bool bf16, bool solo, bool inl, dim3 grid, hipStream_t s, const KPagedParams& P) {
+static int launch_paged_data(bool bf16, bool solo, bool inl, bool two, dim3 grid, hipStream_t s, const KPagedParams& P) {
     using K = void (*)(KPagedParams);
     static const K table[2][2][2] = {
-        {{paged_data_kernel<4, false, false>, paged_data_kernel<4, false, true>},
-         {paged_data_kernel<4, true, false>, paged_data_kernel<4, true, true>}},
-        {{paged_data_kernel<2, false, false>, paged_data_kernel<2, false, true>},
-         {paged_data_kernel<2, true, false>, paged_data_kernel<2, true, true>}}};
+        {{paged_data_kernel<4, false, false, false>, paged_data_kernel<4, false, true, false>},
+         {paged_data_kernel<4, true, false, false>, paged_data_kernel<4, true, true, false>}},
+        {{paged_data_kernel<2, false, false, false>, paged_data_kernel<2, false, true, false>},
+         {paged_data_kernel<2, true, false, false>, paged_data_kernel<2, true, true, false>}}};
+#if LEYLINE_PAIR_F64
+    static const K two_chunk[2][2] = {{paged_data_kernel<2, false, false, true>, paged_data_kernel<2, false, true, true>},
+                                      {paged_data_kernel<2, true, false, true>, paged_data_kernel<2, true, true, true>}};
+    if (bf16 && two) return launch(two_chunk[solo][inl], grid, s, P, PAGED_TPB);
+#endif
+    (void)two;
     return launch(table[bf16][solo][inl], grid, s, P, PAGED_TPB);
 }
 
@@ -2143,7 +2157,11 @@ extern "C" int leyline_splice_paged(const leyline_cache* cache, int32_t n_seqs, 
             P.move_blk_div = make_div(int32_t(std::max<int64_t>(1, mb)));
             P.remap_blk_div = make_div(int32_t(std::max<int64_t>(1, rb)));
             const bool solo = P.move_base[1] == mb && P.remap_base[1] == rb;   // plane 0 only
-            rc = launch_paged_data(bf16, solo, !row_table, dim3(unsigned(blocks)), s, P);
+            bool two = false;                                                  // two-chunk units
+            for (int p = 0; p < n_planes; ++p)
+                if (planes[p].rot == KROT_NEOX && (!planes[p].neox_lanes || planes[p].band_tpr != planes[p].rot_chunks))
+                    two = true;
+            rc = launch_paged_data(bf16, solo, !row_table, two, dim3(unsigned(blocks)), s, P);
             if (rc) return rc;
         }
     }

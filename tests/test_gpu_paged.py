@@ -71,9 +71,13 @@ def _random_workload(rng, page, kind, dtype, max_len=None):
             dirs.append(W.Dir(s, e, r, seq=b))
     if kind == "mla":
         planes = [W.mla_plane()]
-    elif kind == "mla_neox":      # half-split band that straddles wavefront windows: two-chunk units
+    elif kind == "mla_neox":      # half-split rows of 72 chunks: partners in the same wavefront
         planes = [W.PlaneDesc((576,), 1, 576, 512, 64, 1, 10000.0)]
-    elif kind == "gqa8":          # 2 KB rotated per row: re-used pages rotate in physical order
+    elif kind == "heads96":       # heads across wavefront ends: two-chunk units, gathered and in place
+        planes = W.gqa_planes(heads=3, dim=96)
+    elif kind == "heads80":
+        planes = W.gqa_planes(heads=10, dim=80)
+    elif kind == "gqa8":          # 2 KB rotated per row: re-used pages can rotate in physical order
         planes = W.gqa_planes(heads=8, dim=128)
     elif kind == "mla_split":     # K_pe and c_kv in two arrays: a plane that is all rotary band
         planes = W.mla_split_planes()
