@@ -219,9 +219,10 @@ int leyline_splice_contig(const leyline_cache* cache, int64_t seq_len,
  * leyline_splice_contig without any device allocation, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).
  *
- * Same splice, arguments, validation and results as leyline_splice_contig, but the workspace is
- * a fixed array of LEYLINE_SCRATCH_BYTES bytes in device memory that the library holds on each
- * GPU it runs on until the process ends (located on the first call on a device).  The call uses the calling thread's current device; a non-NULL stream must belong to it
+ * Same splice, arguments, validation, kernels and results as leyline_splice_contig, but the
+ * workspace is a fixed array of LEYLINE_SCRATCH_BYTES bytes in device memory that the library
+ * holds on each GPU it runs on until the process ends (located on the first call on a device).
+ * The call uses the calling thread's current device; a non-NULL stream must belong to it
  * (E_INVAL otherwise).  A splice whose ordered tiles need more workspace than
  * LEYLINE_SCRATCH_BYTES returns LEYLINE_E_WORKSPACE before anything is enqueued (1 MiB holds
  * the counters and flags of, e.g., a small-shift splice of a 61-layer MLA cache of about 480K
@@ -229,10 +230,7 @@ int leyline_splice_contig(const leyline_cache* cache, int64_t seq_len,
  * device allocation or free (no hipMalloc / hipFree, no allocating library routine) and clears
  * the counters and flags it needs with a kernel at its start.  Every call on one GPU shares that
  * GPU's array: calls that may overlap in time on one GPU (other streams, other threads) race and
- * must be ordered by the caller.  A cache with a half-split rotary plane whose rows are neither a
- * multiple nor a divisor of 1 KiB is spliced without ordered tiles, in rounds or ordered chains:
- * such calls use no scratch, so they may overlap and no size is refused; small shifts take up to
- * 1.6 times as long as with a caller workspace, and the stored bits are the same.
+ * must be ordered by the caller.
  */
 int leyline_splice_contig_noalloc(const leyline_cache* cache, int64_t seq_len,
                                   const leyline_directive* dirs, int32_t n_dirs,

@@ -1890,12 +1890,11 @@ extern "C" int leyline_splice_contig_noalloc(const leyline_cache* cache, int64_t
     ContigSchedule sched;
     int rc = plan_contig(cache, seq_len, dirs, n_dirs, &sched);
     if (rc) return rc;
-    if (sched.tiles && sched.tiles_optional) {
-        // rows that run without tiles too: such calls share nothing, overlap freely and have no size bound
+    if (sched.ws_bytes > LEYLINE_SCRATCH_BYTES) {
+        if (!sched.tiles_optional) return LEYLINE_E_WORKSPACE;
         rc = plan_contig(cache, seq_len, dirs, n_dirs, &sched, false);
         if (rc) return rc;
     }
-    if (sched.ws_bytes > LEYLINE_SCRATCH_BYTES) return LEYLINE_E_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     char* ws = nullptr;
     if (sched.ws_bytes > 0) {

@@ -63,34 +63,3 @@ def test_ragged_half_split_rows(kind, dtype):
             assert got.value == new_len
             for a, b in zip(planes, other):
                 assert torch.equal(bits(a[:, :new_len]), bits(b[:, :new_len])), f"{kind}/{dtype} n={n} workspace {size}"
-
-
-@pytest.mark.gpu
-@pytest.mark.parametrize("kind", ["mla", "heads5", "heads10", "partial"])
-def test_noalloc_uses_no_shared_scratch(kind):
-    """Ragged half-split rows through the entry without a workspace: no ordered tiles, whose counters and
-    flags would live in the scratch array that all calls on the GPU share; the bits are those of the tiles."""
-    from torch.profiler import ProfilerActivity, profile
-    from paper_2606_01065_amd import leyline as L
-    from tests import test_gpu_contig as TC
-    n, dirs = 1500, [W.Dir(7, 40, 12), W.Dir(300, 310, 50), W.Dir(900, 1000, 1)]
-    wl = TC._small_workload(random.Random(kind), "heads", "bf16", 3, n, dirs)
-    wl.planes = KINDS[kind]
-    planes, stubs = W.alloc_contig(wl, "cuda:0")
-    pristine = [t.clone() for t in planes]
-    dd = L.make_directives(TC._dir_dicts(wl, stubs))
-    names, outs = [], []
-    for call in (L.leyline_splice_contig, L.leyline_splice_contig_noalloc):
-        tensors = [t.clone() for t in pristine]
-        cache = L.make_cache(TC._specs(L, wl, tensors))
-        assert L.leyline_contig_query(cache, n, dd, len(dirs)).tile_launches > 0
-        with profile(activities=[ProfilerActivity.CUDA]) as prof:
-            outs.append((call(cache, n, dd, len(dirs)), tensors))
-            torch.cuda.synchronize()
-        names.append([e.name for e in prof.events() if "contig" in e.name])
-    assert any("contig_tile" in k for k in names[0]), names[0]
-    assert names[1] and not any("contig_tile" in k or "prep" in k for k in names[1]), names[1]
-    (n_ws, a), (n_na, b) = outs
-    assert n_ws == n_na
-    for x, y in zip(a, b):
-        assert torch.equal(bits(x[:, :n_ws]), bits(y[:, :n_ws])), kind
