@@ -194,7 +194,9 @@ int leyline_contig_query(const leyline_cache* cache, int64_t seq_len,
  * (MLA rows of 576 bf16 elements, 5 or 10 heads of 128) also runs without one: given NULL, or a
  * workspace that is misaligned or smaller than the reported size, the call is made in rounds or
  * ordered chains instead of ordered tiles, with the same result bit for bit, and touches no
- * workspace.  Small shifts then take up to 1.6 times as long.
+ * workspace.  Small shifts then take longer, the more the smaller the shift and the fewer the layers:
+ * 27 layers of MLA rows, a 45-token shift 1.6 times, 16K tokens of one layer, a 40-token shift 17 times
+ * as long.
  * device_status: device int32, nullable.  A tile waits for the tiles whose source rows its
  * destination overlaps; each wait is bounded (a few hundred milliseconds at least, where a
  * correct schedule waits microseconds).  A tile that gives up ORs LEYLINE_STATUS_TILE_TIMEOUT
@@ -224,13 +226,15 @@ int leyline_splice_contig(const leyline_cache* cache, int64_t seq_len,
  * holds on each GPU it runs on until the process ends (located on the first call on a device).
  * The call uses the calling thread's current device; a non-NULL stream must belong to it
  * (E_INVAL otherwise).  A splice whose ordered tiles need more workspace than
- * LEYLINE_SCRATCH_BYTES returns LEYLINE_E_WORKSPACE before anything is enqueued (1 MiB holds
- * the counters and flags of, e.g., a small-shift splice of a 61-layer MLA cache of about 480K
- * tokens); use leyline_splice_contig with a caller workspace for those.  The call makes no
+ * LEYLINE_SCRATCH_BYTES returns LEYLINE_E_WORKSPACE before anything is enqueued (but see below;
+ * 1 MiB holds the counters and flags of, e.g., a small-shift splice of a 61-layer MLA cache of about
+ * 480K tokens); use leyline_splice_contig with a caller workspace for those.  The call makes no
  * device allocation or free (no hipMalloc / hipFree, no allocating library routine) and clears
  * the counters and flags it needs with a kernel at its start.  Every call on one GPU shares that
  * GPU's array: calls that may overlap in time on one GPU (other streams, other threads) race and
- * must be ordered by the caller.
+ * must be ordered by the caller, whatever the layout (ordered tiles are used wherever the query
+ * reports a workspace).  A call on a cache that also runs without a workspace (above) is not refused
+ * when its tiles need more than LEYLINE_SCRATCH_BYTES: it then runs without them.
  */
 int leyline_splice_contig_noalloc(const leyline_cache* cache, int64_t seq_len,
                                   const leyline_directive* dirs, int32_t n_dirs,

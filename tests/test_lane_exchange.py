@@ -63,3 +63,30 @@ def test_ragged_half_split_rows(kind, dtype):
             assert got.value == new_len
             for a, b in zip(planes, other):
                 assert torch.equal(bits(a[:, :new_len]), bits(b[:, :new_len])), f"{kind}/{dtype} n={n} workspace {size}"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layers", [3, 60000])
+def test_noalloc_within_and_beyond_its_scratch(layers):
+    """Ragged half-split rows through the entry without a workspace: as ordered tiles in the library's scratch
+    array, or (five edits of 60,000 layers need 300,000 flags of 4 bytes) without them; the same bits."""
+    from paper_2606_01065_amd import leyline as L
+    from tests import test_gpu_contig as TC
+    n, dirs = 60, [W.Dir(3, 5, 1)] + [W.Dir(27 + 6 * i, 29 + 6 * i, 1) for i in range(4)]   # 22 rows by -1 first
+    wl = W.Workload("noalloc_half", 1, "bf16", KINDS["mla"], dirs, [n], capacity=n, seed=11)
+    (one,), stubs1 = W.alloc_contig(wl, "cuda:0")
+    stubs = [[s.expand(layers, *s.shape[1:]).contiguous() for s in per] for per in stubs1]
+    dd = L.make_directives([dict(span_start=d.span_start, span_end=d.span_end, stub=stubs[j], stub_len=1)
+                            for j, d in enumerate(dirs)])
+    outs = []
+    for call in (L.leyline_splice_contig, L.leyline_splice_contig_noalloc):
+        t = one.expand(layers, *one.shape[1:]).contiguous()
+        cache = L.make_cache(TC._specs(L, wl, [t]))
+        assert (L.leyline_contig_query(cache, n, dd, 5).workspace_bytes > L.SCRATCH_BYTES) == (layers > 3)
+        print(f"[case] no-alloc ragged half-split, {layers} layers, {call.__name__}", flush=True)
+        assert call(cache, n, dd, 5) == n - 5
+        torch.cuda.synchronize()
+        assert torch.equal(bits(t), bits(t[:1]).expand_as(t)), "layers differ"
+        outs.append(t[0, :n - 5].clone())
+    assert torch.equal(bits(outs[0]), bits(outs[1]))
+    assert not torch.equal(bits(outs[0]), bits(one[0, :n - 5]))
