@@ -27,9 +27,9 @@
 // few large rounds, the whole call (every move and replacement copy) runs as ordered tiles:
 // workgroups take tickets in start order and wait on per-tile "source read" flags, so that no
 // tile overwrites rows another tile has still to read (contig_tile_kernel).  Layouts whose
-// half-split partners cannot be exchanged between lanes use ordered chains instead: chain c owns
-// rows c, c+m, c+2m, ... and one thread walks it in order, overwriting only rows it has already
-// read itself.
+// half-split partners cannot be exchanged between lanes use ordered chains instead, and so do ragged
+// half-split rows in a call without a workspace: chain c owns rows c, c+m, c+2m, ... and one thread
+// walks it in order, overwriting only rows it has already read itself.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -663,8 +663,9 @@ __global__ __launch_bounds__(MOVE_TPB) void contig_move_kernel(const KContigPara
     }
 }
 
-// Ordered chains (shifts too small for rounds, on layouts whose half-split partners cannot be
-// exchanged between lanes, so tiles are not used): thread (chain c, unit u) walks rows c, c+m, ...
+// Ordered chains (shifts too small for rounds where tiles are not used: half-split partners that cannot
+// be exchanged between lanes, or ragged half-split rows without a workspace, see
+// ContigSchedule::tiles_optional): thread (chain c, unit u) walks rows c, c+m, ...
 template <int ESZ>
 __global__ __launch_bounds__(TPB) void contig_chain_kernel(const KContigParams P) {
     const KItem& I = P.items[blockIdx.z];

@@ -120,8 +120,8 @@ constexpr int KMAX_CS = LEYLINE_PAIR_F64 ? 120 : 192;
 enum : int32_t {
     KJOB_ROUND = 0,   // rows [src0, src0+count) move by delta with count <= |delta|: sources and
                       // destinations are disjoint, one chunk per thread
-    KJOB_CHAIN = 1,   // rows [src0, src0+count) move by delta, count > |delta|: ordered chains
-                      // (layouts whose half-split partners need two-chunk units)
+    KJOB_CHAIN = 1,   // rows [src0, src0+count) move by delta, count > |delta|: ordered chains, in
+                      // two-chunk units (half-split rows that have no tiles, or no workspace for them)
     KJOB_STUB = 2,    // count replacement rows copied to [dst0, dst0+count)
     KJOB_TILE = 3     // rows [src0, src0+count) move by delta as ordered tiles
 };

@@ -36,9 +36,9 @@ int resolve_forget(const leyline_directive* dirs, int32_t n_dirs, int32_t n_seqs
                    const int32_t* seq_lens, int64_t seq_len, std::vector<leyline_directive>* buf,
                    const leyline_directive** use);
 
-// cos/sin of (shift * theta_i), evaluated in fp64 and rounded to fp32, for every rotary pair of
-// every rotary plane.  The frequencies, a third of the cost, are evaluated once per call, and a shift
-// that repeats the one before it is copied.
+// cos/sin of (shift * theta_i), evaluated in fp64 and rounded to kcs_t, for every rotary pair of
+// every rotary plane.  The frequencies are evaluated once per call, and a shift that repeats the one
+// before it is copied.
 class ShiftTable {
 public:
     explicit ShiftTable(const leyline_cache* cache) : cache_(cache) {}

@@ -91,9 +91,11 @@ def _random_workload(rng, page, kind, dtype, max_len=None):
 
 
 @pytest.mark.parametrize("kind,dtype", [("mla", "bf16"), ("gqa", "bf16"), ("mla", "f32"),
-                                        ("gqa", "f32"), ("mla_neox", "bf16"), ("four", "bf16")])
+                                        ("gqa", "f32"), ("mla_neox", "bf16"), ("four", "bf16"),
+                                        ("heads96", "bf16"), ("heads80", "bf16"), ("heads96", "f32")])
 def test_small_random_paged_whole_pool(L, kind, dtype):
-    rng = random.Random({"mla": 97, "gqa": 98, "mla_neox": 99, "four": 100}[kind] + (dtype == "f32"))
+    rng = random.Random({"mla": 97, "gqa": 98, "mla_neox": 99, "four": 100, "heads96": 102,
+                         "heads80": 104}[kind] + (dtype == "f32"))
     for page in (1, 4, 16, 64):
         for ci in range(8):
             wl = _random_workload(rng, page, kind, dtype)
@@ -117,11 +119,11 @@ def test_small_random_paged_whole_pool(L, kind, dtype):
                 assert_rows_match(got, want[pi], plane, dtype, what=f"page={page} case={ci} plane={pi}")
 
 
-@pytest.mark.parametrize("kind", ["mla", "gqa"])
+@pytest.mark.parametrize("kind", ["mla", "gqa", "heads96", "heads80"])
 def test_page_sizes_not_powers_of_two(L, kind):
     """Pages of 3 and 48 rows: page and row index arithmetic without power-of-two shortcuts;
     whole pools against the oracle."""
-    rng = random.Random({"mla": 401, "gqa": 402}[kind])
+    rng = random.Random({"mla": 401, "gqa": 402, "heads96": 403, "heads80": 404}[kind])
     for page in (3, 48):
         for ci in range(5):
             wl = _random_workload(rng, page, kind, "bf16")
@@ -247,10 +249,11 @@ def test_out_of_pool_pages_are_flagged_and_skipped(L):
 
 @pytest.mark.parametrize("kind", ["mla", "gqa"])
 @pytest.mark.parametrize("last_stub", [256, 257])
-def test_inline_and_row_table_gathers(L, kind, last_stub):
+def test_gathers_of_1024_and_1025_rows(L, kind, last_stub):
     """Token-slot cache, four directives: the downstream slots form four REMAP runs whose
-    boundaries fall inside workgroups, and the replacements total 1024 rows (gathered without a
-    row table, one launch) or 1025 (row table); whole pool against the oracle."""
+    boundaries fall inside workgroups, and the replacements total 1024 rows or 1025, the first count
+    whose route depends on more than itself (few spans and few bytes: one launch, like 1024); whole
+    pool against the oracle."""
     dirs = [W.Dir(500, 600, 256), W.Dir(1500, 1510, 256), W.Dir(2500, 2700, 256), W.Dir(4000, 4001, last_stub)]
     planes = [W.mla_plane()] if kind == "mla" else W.gqa_planes(heads=2, dim=128)
     wl = W.Workload(f"slots_{kind}", 2, "bf16", planes, dirs, [5000], page_size=1, seed=61 + last_stub)
@@ -277,12 +280,13 @@ def test_inline_and_row_table_gathers(L, kind, last_stub):
 
 @pytest.mark.parametrize("kind,dtype", [("mla", "bf16"), ("gqa", "bf16"), ("mla", "f32"),
                                         ("mla_neox", "bf16"), ("four", "bf16"), ("gqa8", "bf16"),
-                                        ("gqa8", "f32")])
+                                        ("gqa8", "f32"), ("heads96", "bf16"), ("heads80", "f32")])
 def test_token_slot_paged_whole_pool(L, kind, dtype):
     """Page sizes 1 and 2 (token-slot caches) with sequences long enough that the in-place
-    rotation of remapped slots spans many workgroups and ends in a ragged one.  With 8 GQA heads
-    (2 KB or more rotated per row) the re-used slots are first sorted by physical slot."""
-    rng = random.Random({"mla": 197, "gqa": 198, "mla_neox": 199, "four": 200, "gqa8": 201}[kind] + (dtype == "f32"))
+    rotation of remapped slots spans many workgroups and ends in a ragged one, in plan order (these
+    calls rotate too little to sort their slots first; test_gpu_gather_routes.py has ones that do)."""
+    rng = random.Random({"mla": 197, "gqa": 198, "mla_neox": 199, "four": 200, "gqa8": 201, "heads96": 203,
+                         "heads80": 205}[kind] + (dtype == "f32"))
     for page in (1, 2):
         for ci in range(3):
             wl = _random_workload(rng, page, kind, dtype, max_len=900)
