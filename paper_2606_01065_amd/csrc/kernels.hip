@@ -66,8 +66,10 @@ constexpr int TPB = LEYLINE_TPB;
 #endif
 constexpr int CRPT = LEYLINE_CONTIG_RPT;   // rows per thread of a rotating round item
 // Rows per thread of a round-kernel item: CRPT when it rotates, one when it only copies (a V plane, a
-// replacement copy); with fp64 pairs, copies of CRPT / one row: GQA 16K splice 575 / 556 us, split MLA
-// 32K splice 613 / 576 us.  The kernel and the launcher's grid both take it from here.
+// replacement copy).  With fp64 pairs, copies of CRPT / one row, the device in steady use: GQA 16K splice
+// 567 / 554 us, split MLA 32K 472 / 450, 3 heads of 96 672 / 604; in the first twenty splices of a
+// process, while its clocks still rise, it is the other way round (GQA 16K 459 / 505 us, split MLA 336 /
+// 367).  The kernel and the launcher's grid both take it from here.
 LEYLINE_HD inline int round_rows_per_thread(bool rotates) { return rotates ? CRPT : 1; }
 constexpr int MOVE_TPB = LEYLINE_MOVE_TPB; // its workgroup size
 #ifndef LEYLINE_GATHER_SPLIT_PAGE

@@ -269,6 +269,26 @@ def mla_dsv3_rotate_split_32k() -> Workload:
     """mla_dsv3_rotate_32k with K_pe and c_kv in separate arrays."""
     return _split(mla_dsv3_rotate_32k(), "mla_dsv3_rotate_split_32k")
 
+def mla_half_8k_message() -> Workload:
+    """An edited message on a 27-layer 8K-token MLA cache whose rotary pairs are half-split: rows of
+    72 chunks, a shift of -45, ordered tiles."""
+    return Workload("mla_half_8k_message", 27, "bf16", [PlaneDesc((576,), 1, 576, 512, 64, 1, 10000.0)],
+                    [Dir(3000, 3120, 75)], [8192], capacity=8192, seed=18)
+
+
+def gqa_1head_pages16_4k() -> Workload:
+    """An edited message on the 16-token pages of a 4K-token request, one KV head to a rank: about
+    3,000 rows gathered in one launch."""
+    return Workload("gqa_1head_pages16_4k", 32, "bf16", gqa_planes(heads=1), [Dir(1000, 1048, 70)], [4096],
+                    page_size=16, seed=19)
+
+
+def gqa_llama3_8b_slots_4k() -> Workload:
+    """A 512-token eviction from a 4K-token GQA cache on token slots: 3,072 K rows rotated in place in
+    plan order (400 MB, below the sort's bound)."""
+    return Workload("gqa_llama3_8b_slots_4k", 32, "bf16", gqa_planes(), [Dir(512, 1024, 24)], [4096],
+                    page_size=1, seed=20)
+
 
 WORKLOADS = {
     "mla_1l_4k_f32": mla_1l_4k_f32,
@@ -288,6 +308,9 @@ WORKLOADS = {
     "mla_dsv3_32k_split": mla_dsv3_32k_split,
     "mla_dsv3_slots_split_32k": mla_dsv3_slots_split_32k,
     "mla_dsv3_rotate_split_32k": mla_dsv3_rotate_split_32k,
+    "mla_half_8k_message": mla_half_8k_message,
+    "gqa_1head_pages16_4k": gqa_1head_pages16_4k,
+    "gqa_llama3_8b_slots_4k": gqa_llama3_8b_slots_4k,
 }
 
 
